@@ -57,7 +57,9 @@
 #include <vector>
 
 #include "sq_device.h"
+#include "sq_gemm_args.h"
 #include "sq_launch.h"
+#include "sq_thin.h"
 
 namespace sq {
 
@@ -71,123 +73,6 @@ namespace sq {
 enum Mode { kDx = 1, kDs = 2, kFwdR = 3, kFwdC = 4 };
 
 constexpr int kBK = 64;                 // K per LDS stage
-constexpr int kXcds = 8;                // MI355X: workgroups are dealt round-robin to 8 XCDs
-constexpr uint32_t kOOB = 0x80000000u;  // a buffer offset past every operand: reads zero
-
-#define SQ_LDS __attribute__((address_space(3)))
-typedef short v4i16 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-struct GemmArgs {
-  const uint16_t* a;      // FWD: X [T,I]   DX: dY [T,O]   DS: X [T,I]
-  const uint16_t* b;      // DS: dY [T,O]
-  const uint8_t* codes;   // [O, I/2]
-  const uint8_t* scales;  // [O, G]  (FWD, DX)
-  void* out;              // FWD: Y [T,O]  DX: dX [T,I]  DS: dS [O,G] fp32
-  int M, N, K;
-  int T, O, I, G;
-  float ws2;              // NV epilogue factor (1 for MX)
-  int out_bf16;
-  int ksplit;             // DS: K (token) ranges per tile; >1 writes partial planes to `out`
-  int ksteps_per;         // DS: K stages per range
-  // the launch covers output rows [m_off, m_off + m_cnt) and columns
-  // [n_off, n_off + n_cnt) (a count of 0: up to M or N)
-  int m_off, m_cnt, n_off, n_cnt;
-};
-
-// Up to kGroupMax experts per grouped launch, passed by value (kernel
-// arguments stay under 4 KiB): each kind of pointer is a base and a 32-bit
-// byte offset per expert, so the run of experts a launch takes is cut short
-// where the pointers of one kind would span 4 GiB or more.  The second
-// operand is dS's dY, or the forward's and dX's scale plane.  An operand an
-// expert does not have (null, read with a size of zero) gets offset 0.
-struct GemmGroup {
-  GemmArgs base;                  // shared: O, I, G, N (fwd/dx) or M, N (ds), out_bf16
-  const uint8_t* a0;
-  const uint8_t* p0;
-  const uint8_t* codes0;
-  uint8_t* out0;
-  uint32_t a[kGroupMax];
-  uint32_t p[kGroupMax];
-  uint32_t codes[kGroupMax];
-  uint32_t out[kGroupMax];
-  int T[kGroupMax];
-  float ws2[kGroupMax];
-  int tile_begin[kGroupMax];
-  int count;
-  __device__ const uint16_t* act(int e) const { return reinterpret_cast<const uint16_t*>(a0 + a[e]); }
-  __device__ const uint8_t* second(int e) const { return p0 + p[e]; }
-  __device__ const uint8_t* code_plane(int e) const { return codes0 + codes[e]; }
-  __device__ void* output(int e) const { return out0 + out[e]; }
-};
-static_assert(sizeof(GemmGroup) <= 4096, "kernel argument budget");
-
-// Bases and offsets of experts p[0, n) (dS: the second operand is b, else
-// the scale plane); false when one kind's pointers span 4 GiB or more.
-static bool set_experts(GemmGroup& gg, const ExpertProblem* p, int n, bool ds) {
-  auto pack = [&](auto get, const uint8_t*& base, uint32_t* off) {
-    uintptr_t lo = UINTPTR_MAX, hi = 0;
-    for (int e = 0; e < n; ++e) {
-      const uintptr_t v = reinterpret_cast<uintptr_t>(get(p[e]));
-      if (v == 0) continue;
-      lo = v < lo ? v : lo;
-      hi = v > hi ? v : hi;
-    }
-    if (lo == UINTPTR_MAX) lo = hi = 0;
-    if (hi - lo > 0xFFFFFFFFu) return false;
-    base = reinterpret_cast<const uint8_t*>(lo);
-    for (int e = 0; e < n; ++e) {
-      const uintptr_t v = reinterpret_cast<uintptr_t>(get(p[e]));
-      off[e] = v == 0 ? 0u : (uint32_t)(v - lo);
-    }
-    return true;
-  };
-  const uint8_t* out0 = nullptr;
-  const bool ok = pack([](const ExpertProblem& x) { return x.a; }, gg.a0, gg.a) &&
-                  pack([ds](const ExpertProblem& x) { return ds ? x.b : static_cast<const void*>(x.scales); },
-                       gg.p0, gg.p) &&
-                  pack([](const ExpertProblem& x) { return x.codes; }, gg.codes0, gg.codes) &&
-                  pack([](const ExpertProblem& x) { return x.out; }, out0, gg.out);
-  gg.out0 = const_cast<uint8_t*>(out0);
-  return ok;
-}
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
-}
-
-// Buffer descriptor of the global -> LDS copies: base, num_records = bytes
-// (offsets at or past it read zeros), raw buffer flags.
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-struct DmaRsrc {
-  i32x4 v;
-};
-__device__ __forceinline__ DmaRsrc make_dma_rsrc(const void* p, uint32_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(p);
-  DmaRsrc r;
-  r.v = i32x4{__builtin_amdgcn_readfirstlane((int)(uint32_t)a), __builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32) & 0xFFFF),
-              __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
-  return r;
-}
-
-// 16 bytes per lane, global -> LDS; lane l writes dst + 16 l.  Written as
-// the instruction itself: the compiler's wait insertion cannot tell the LDS
-// tile a copy fills from the tile being read, and would otherwise stall
-// every later LDS read until the copy lands.  The loop waits for the copies
-// explicitly (vmcnt) before the barrier that publishes a stage.
-__device__ __forceinline__ void dma16(DmaRsrc r, SQ_LDS void* dst, uint32_t voff) {
-  const int lds = __builtin_amdgcn_readfirstlane((int)(uint32_t)reinterpret_cast<uintptr_t>(dst));
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(r.v)
-               : "memory", "m0");
-}
-
-// Wait until at most n vector-memory loads of this wave are outstanding and
-// all of its LDS operations are done (raw s_barrier has no memory semantics).
-template <int n>
-__device__ __forceinline__ void wait_vm_lgkm0() {
-  static_assert(n >= 0 && n < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt(0x0070 | (n & 15) | ((n >> 4) << 14));
-}
 
 // ------------------------------------------------------------------ layouts
 // KC: K-contiguous [rows][64] bf16; 16-byte chunk c of row r lives at chunk
@@ -366,13 +251,6 @@ constexpr int group_m() {
   return MODE == kDs ? 8 : 4;
 }
 
-// Position in the tile order of workgroup bid of nb: XCD x = bid % 8 takes
-// the x-th contiguous stretch of the order (stretches differ by at most one).
-__device__ __forceinline__ int xcd_stretch(int bid, int nb) {
-  const int x = bid % kXcds, q = nb / kXcds, r = nb % kXcds;
-  return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + bid / kXcds;
-}
-
 // Tile (tm, tn) at position idx of the grouped column-by-column order.
 template <int kGroupM>
 __device__ __forceinline__ void tile_at(int idx, int tiles_m, int tiles_n, int& tm, int& tn) {
@@ -515,7 +393,6 @@ __device__ __forceinline__ void ds_codes(u32x4 (&cw)[TM * TN], const uint8_t* co
       if constexpr (FMT == kMX) {
         cw[j * TM + i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0));
       } else {
-        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
         const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off, 0, 0));
         const u32x2 hi = __builtin_bit_cast(
             u32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(off == kOOB ? kOOB : off + 8u), 0, 0));
@@ -582,8 +459,13 @@ __device__ __forceinline__ void ds_store(const f32x16 (&acc)[TM][TN], const u32x
 // product, dealt to XCDs by bid % 8; with ORDERED, bid is already the tile's
 // position in the product's tile order (the grouped launch deals its XCD
 // stretches over all experts at once).
-template <int MODE, int FMT, int BM, int BN, int WGM, int WGN, int STAGES, int BK, bool ORDERED = false>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bid, int nb) {
+// With THIN the workgroup may instead take a strip of an expert with few
+// tokens (thin_strip): a grouped call whose experts are mostly larger runs its
+// few small ones in the same launch.
+constexpr int kFuseNt = 2;                     // a fused strip: 16 tokens x 32 columns
+template <int MODE, int FMT, int BM, int BN, int WGM, int WGN, int STAGES, int BK, bool ORDERED = false,
+          bool THIN = false>
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bid, int nb, bool thin_strip = false) {
   constexpr int NT = 64 * WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int TM = WM / 32, TN = WN / 32;
@@ -630,6 +512,29 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bid, int nb) {
   else tile_of<group_m<MODE>()>((MODE == kDs && g.ksplit > 1) ? bid - split * tiles : bid, (MODE == kDs && g.ksplit > 1) ? tiles : nb,
                                 tiles_m, tiles_n, tm, tn);
   const int m0 = g.m_off + tm * BM, n0 = g.n_off + tn * BN;
+
+  if constexpr (THIN) {
+    if (thin_strip) {
+      constexpr int kWave = MODE == kDx ? thin_dx_wave_bytes<1, 1>() : thin_fwd_wave_bytes<1, kFuseNt, 1>();
+      constexpr int kPer = L::kStageAlloc / kWave, kPerW = (kWReg ? L::kWBytes : 0) / kWave;
+      static_assert(NT == kThinThreads && STAGES != 3 && STAGES * kPer + kPerW >= kThinKWaves, "a region per wave");
+      auto region = [&](int w) -> SQ_LDS uint8_t* {
+        if (w < kPerW) return (SQ_LDS uint8_t*)ldsw + w * kWave;
+        w -= kPerW;
+        if (w < kPer) return (SQ_LDS uint8_t*)lds0 + w * kWave;
+        if constexpr (STAGES > 2) {
+          if (w >= 2 * kPer)
+            return w < 3 * kPer ? (SQ_LDS uint8_t*)lds2 + (w - 2 * kPer) * kWave
+                                : (SQ_LDS uint8_t*)lds3 + (w - 3 * kPer) * kWave;
+        }
+        return (SQ_LDS uint8_t*)lds1 + (w - kPer) * kWave;
+      };
+      const int tiles_t = (g.T + 15) / 16;
+      if constexpr (MODE == kDx) thin_dx_tile<FMT, 1, 1>(g, bid % tiles_t, bid / tiles_t, region);
+      else thin_fwd_tile<FMT, 1, kFuseNt, 1>(g, bid % tiles_t, bid / tiles_t, region);
+      return;
+    }
+  }
 
   auto stage = [&](auto SC) -> SQ_LDS uint8_t* {
     constexpr int S = decltype(SC)::value;
@@ -843,7 +748,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bid, int nb) {
     if constexpr (MODE == kFwdC) {
 #pragma unroll
       for (int j = 0; j < kSc; ++j) {
-        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
         const uint32_t off = sc0[j] + 16u * (uint32_t)chunk;
         const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rs_sc, (int)off, 0, 0));
         const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rs_sc, (int)(off + 8u), 0, 0));
@@ -1179,7 +1083,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmArgs g) {
 // L2 and read its activation and weight panels from HBM about once; dealing
 // every expert's tiles over all 8 XCDs made each L2 fetch them again (the
 // 128-expert MoE layer moved 4 to 8 times its operand bytes).
-template <int MODE, int FMT, int BM, int BN, int WGM, int WGN, int STAGES, int BK>
+template <int MODE, int FMT, bool THIN, int BM, int BN, int WGM, int WGN, int STAGES, int BK>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_grouped_kernel(GemmGroup gg) {
   const int b = xcd_stretch((int)blockIdx.x, (int)gridDim.x);
   int lo = 0, hi = gg.count - 1;                 // last e with tile_begin[e] <= b
@@ -1199,10 +1103,12 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_grouped_kernel(GemmGroup 
   g.ws2 = gg.ws2[e];
   if (MODE == kDs) g.K = g.T;
   else g.M = g.T;
-  const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
+  const bool strip = THIN && thin_takes(g.T, g.K);
+  const int tiles = strip ? ((g.T + 15) / 16) * ((g.N + 16 * kFuseNt - 1) / (16 * kFuseNt))
+                          : ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   const int local = b - gg.tile_begin[e];
   if (local >= tiles) return;
-  gemm_tile<MODE, FMT, BM, BN, WGM, WGN, STAGES, BK, true>(g, local, tiles);
+  gemm_tile<MODE, FMT, BM, BN, WGM, WGN, STAGES, BK, true, THIN>(g, local, tiles, strip);
 }
 
 // Streamed grouped dS.  With a few hundred tokens per expert a dS tile holds
@@ -1436,7 +1342,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void ds_stream_kernel(GemmGroup gg)
 #define SQ_CFG_DS 256, 256, 2, 4, 2, 64
 #define SQ_CFG_FWDC 256, 256, 2, 4, 2, 64
 #define SQ_CFG_SMALL 128, 128, 2, 4, 2, 64
-constexpr int kCUs = 256;   // MI355X compute units
 
 template <int MODE, int FMT, int BM, int BN, int WGM, int WGN, int STAGES, int BK>
 static int launch_gemm(const GemmArgs& g, hipStream_t s) {
@@ -1522,6 +1427,66 @@ static bool regs_dequant_ok(int G, const ExpertProblem* p, int n) {
   return true;
 }
 
+// ------------------------------------------------------------------ few tokens
+template <int FMT, int MT, int NT, int D>
+static int thin_fwd_go(const GemmArgs* one, GemmGroup* gg, hipStream_t s) {
+  if (one) {
+    const int tm = (one->T + 16 * MT - 1) / (16 * MT), tn = (one->O + 16 * NT - 1) / (16 * NT);
+    hipLaunchKernelGGL((thin_fwd_kernel<FMT, MT, NT, D>), dim3((unsigned)(tm * tn)), dim3(kThinThreads), 0, s, *one, tm);
+  } else {
+    int blocks = 0;
+    for (int e = 0; e < gg->count; ++e) {
+      gg->tile_begin[e] = blocks;
+      blocks += (gg->T[e] + 16 * MT - 1) / (16 * MT) * ((gg->base.O + 16 * NT - 1) / (16 * NT));
+    }
+    hipLaunchKernelGGL((thin_fwd_grouped_kernel<FMT, MT, NT, D>), dim3((unsigned)blocks), dim3(kThinThreads), 0, s, *gg);
+  }
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+template <int FMT>
+static int thin_fwd(const GemmArgs* one, GemmGroup* gg, hipStream_t s) {
+  const ThinPick p = one ? thin_fwd_pick(FMT, &one->T, 1, one->O) : thin_fwd_pick(FMT, gg->T, gg->count, gg->base.O);
+  switch (p.mt * 10 + p.nt) {
+    case 11: return thin_fwd_go<FMT, 1, 1, 2>(one, gg, s);
+    case 12: return thin_fwd_go<FMT, 1, 2, 1>(one, gg, s);
+    case 14: return thin_fwd_go<FMT, 1, 4, 1>(one, gg, s);
+    case 21: return thin_fwd_go<FMT, 2, 1, 1>(one, gg, s);
+    case 22: return thin_fwd_go<FMT, 2, 2, 1>(one, gg, s);
+    case 24: return thin_fwd_go<FMT, 2, 4, 1>(one, gg, s);
+    case 41: return thin_fwd_go<FMT, 4, 1, 1>(one, gg, s);
+    case 42: return thin_fwd_go<FMT, 4, 2, 1>(one, gg, s);
+    default: return thin_fwd_go<FMT, 4, 4, 1>(one, gg, s);
+  }
+}
+
+// dX strips are 32 input features wide; their token tile follows the largest
+// token count (4096 x 4096 at 64 tokens 42.4 -> 14 us, 14336 x 4096 135 -> 41,
+// 4096 x 14336 43 -> 30; more tokens in flight per wave, D = 2, ran slower).
+template <int FMT, int MT>
+static int thin_dx_go(const GemmArgs* one, GemmGroup* gg, hipStream_t s) {
+  const int strips = ((one ? one->I : gg->base.I) + kThinDxCols - 1) / kThinDxCols;
+  if (one) {
+    const int tm = (one->T + 16 * MT - 1) / (16 * MT);
+    hipLaunchKernelGGL((thin_dx_kernel<FMT, MT, 1>), dim3((unsigned)(tm * strips)), dim3(kThinThreads), 0, s, *one, tm);
+  } else {
+    int blocks = 0;
+    for (int e = 0; e < gg->count; ++e) {
+      gg->tile_begin[e] = blocks;
+      blocks += (gg->T[e] + 16 * MT - 1) / (16 * MT) * strips;
+    }
+    hipLaunchKernelGGL((thin_dx_grouped_kernel<FMT, MT, 1>), dim3((unsigned)blocks), dim3(kThinThreads), 0, s, *gg);
+  }
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+template <int FMT>
+static int thin_dx(const GemmArgs* one, GemmGroup* gg, hipStream_t s) {
+  int most = one ? one->T : 0;
+  for (int e = 0; gg && e < gg->count; ++e) most = gg->T[e] > most ? gg->T[e] : most;
+  if (most <= 16) return thin_dx_go<FMT, 1>(one, gg, s);
+  if (most <= 32) return thin_dx_go<FMT, 2>(one, gg, s);
+  return thin_dx_go<FMT, 4>(one, gg, s);
+}
+
 // ------------------------------------------------------------------ entry
 int gemm_fwd(int fmt, int T, int O, int I, const void* X, const uint8_t* codes,
              const uint8_t* scales, float ws2, void* Y, int y_bf16, hipStream_t s) {
@@ -1534,6 +1499,7 @@ int gemm_fwd(int fmt, int T, int O, int I, const void* X, const uint8_t* codes,
   g.out_bf16 = y_bf16;
   // registers dequantise when the code and scale planes are 16-byte aligned
   // and every row's scales split into 16-byte runs
+  if (thin_takes(T, I)) return fmt == kMX ? thin_fwd<kMX>(&g, nullptr, s) : thin_fwd<kNV>(&g, nullptr, s);
   ExpertProblem one{};
   one.codes = codes;
   one.scales = scales;
@@ -1550,12 +1516,17 @@ int gemm_dx(int fmt, int T, int O, int I, const void* dY, const uint8_t* codes,
   g.M = T; g.N = I; g.K = O;
   g.ws2 = (fmt == kNV) ? ws2 : 1.0f;
   g.out_bf16 = dx_bf16;
+  if (thin_takes(T, O)) return fmt == kMX ? thin_dx<kMX>(&g, nullptr, s) : thin_dx<kNV>(&g, nullptr, s);
   return fmt == kMX ? launch_sized<kDx, kMX, SQ_CFG_DX>(g, s) : launch_sized<kDx, kNV, SQ_CFG_DX>(g, s);
 }
 
 // ------------------------------------------------------------------ grouped
 // One launch per kGroupMax experts, one workgroup per tile.
-template <int MODE, int FMT, int BM, int BN, int WGM, int WGN, int STAGES, int BK>
+// THIN: experts that take the few-token kernels (thin_takes) run as strips of
+// 16 tokens x 32 columns in the same launch, so the odd one among larger
+// experts costs no launch of its own.
+static_assert(kThinDxCols == 16 * kFuseNt, "one strip width");
+template <int MODE, int FMT, bool THIN, int BM, int BN, int WGM, int WGN, int STAGES, int BK>
 static int launch_grouped(GemmGroup& gg, const ExpertProblem* p, int n, hipStream_t s) {
   using L = SmemLayout<MODE, BM, BN, STAGES, BK, WGM * WGN>;
   static_assert(L::kBytes <= 160 * 1024, "LDS budget");
@@ -1563,14 +1534,16 @@ static int launch_grouped(GemmGroup& gg, const ExpertProblem* p, int n, hipStrea
   gg.count = n;
   for (int e = 0; e < n; ++e) {
     const int M = MODE == kDs ? gg.base.M : p[e].T;
-    const int tiles = ((M + BM - 1) / BM) * ((gg.base.N + BN - 1) / BN);
+    const int tiles = THIN && thin_takes(p[e].T, gg.base.K)
+                          ? ((M + 15) / 16) * ((gg.base.N + 16 * kFuseNt - 1) / (16 * kFuseNt))
+                          : ((M + BM - 1) / BM) * ((gg.base.N + BN - 1) / BN);
     gg.T[e] = p[e].T;
     gg.ws2[e] = FMT == kNV ? p[e].ws2 : 1.0f;
     gg.tile_begin[e] = blocks;
     blocks += tiles;
   }
   if (blocks == 0) return 0;
-  hipLaunchKernelGGL((gemm_grouped_kernel<MODE, FMT, BM, BN, WGM, WGN, STAGES, BK>), dim3(blocks),
+  hipLaunchKernelGGL((gemm_grouped_kernel<MODE, FMT, THIN, BM, BN, WGM, WGN, STAGES, BK>), dim3(blocks),
                      dim3(64 * WGM * WGN), 0, s, gg);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -1623,11 +1596,12 @@ static int launch_ds_stream(GemmGroup& gg, const ExpertProblem* p, int n, hipStr
 // 1920 tiles to 1536 and 192: 175 -> 180 us, so it stays whole).  If the
 // moved pointers do not fit the launch's 32-bit offsets, the experts run
 // unsplit.
-template <int FMT>
+template <int FMT, bool THIN>
 static int dx_split_tails(GemmGroup& gg, const ExpertProblem* p, int n, hipStream_t s) {
   const int64_t cols = (gg.base.I + 127) / 128, cols_thin = (gg.base.I + 255) / 256;
   int64_t all = 0, kept = 0, moved = 0;
   for (int e = 0; e < n; ++e) {
+    if (THIN && thin_takes(p[e].T, gg.base.O)) continue;          // its own strips, in the first launch
     const int t = p[e].T % 128;
     all += (int64_t)((p[e].T + 127) / 128) * cols;
     if (t > 0 && t <= 64) {
@@ -1639,13 +1613,13 @@ static int dx_split_tails(GemmGroup& gg, const ExpertProblem* p, int n, hipStrea
   }
   const double slots = 2.0 * kCUs;
   if (moved == 0 || (double)kept / slots + 1.15 * (double)((moved + 2 * kCUs - 1) / (2 * kCUs)) >= (double)all / slots)
-    return launch_grouped<kDx, FMT, SQ_CFG_SMALL>(gg, p, n, s);
+    return launch_grouped<kDx, FMT, THIN, SQ_CFG_SMALL>(gg, p, n, s);
   ExpertProblem whole[kGroupMax], tail[kGroupMax];
   int nw = 0, nt = 0;
   const size_t a_row = (size_t)gg.base.O * 2, out_row = (size_t)gg.base.I * (gg.base.out_bf16 ? 2 : 4);
   for (int e = 0; e < n; ++e) {
     const int t = p[e].T % 128;
-    if (t == 0 || t > 64) {
+    if (t == 0 || t > 64 || (THIN && thin_takes(p[e].T, gg.base.O))) {
       whole[nw++] = p[e];
       continue;
     }
@@ -1661,10 +1635,32 @@ static int dx_split_tails(GemmGroup& gg, const ExpertProblem* p, int n, hipStrea
   }
   GemmGroup gw = gg, gt = gg;
   if (nt == 0 || !set_experts(gw, whole, nw, false) || !set_experts(gt, tail, nt, false))
-    return launch_grouped<kDx, FMT, SQ_CFG_SMALL>(gg, p, n, s);
-  const int rc = nw > 0 ? launch_grouped<kDx, FMT, SQ_CFG_SMALL>(gw, whole, nw, s) : 0;
+    return launch_grouped<kDx, FMT, THIN, SQ_CFG_SMALL>(gg, p, n, s);
+  const int rc = nw > 0 ? launch_grouped<kDx, FMT, THIN, SQ_CFG_SMALL>(gw, whole, nw, s) : 0;
   if (rc != 0) return rc;
-  return launch_grouped<kDx, FMT, SQ_CFG_GROUPED_THIN>(gt, tail, nt, s);
+  return launch_grouped<kDx, FMT, false, SQ_CFG_GROUPED_THIN>(gt, tail, nt, s);
+}
+
+// Experts that take the few-token kernels run in those when the set holds no
+// others, and share the launch of the small tiles otherwise.
+template <int MODE, int FMT, bool THIN>
+static int grouped_small(GemmGroup& gg, const ExpertProblem* p, int n, int64_t tokens, int64_t others, hipStream_t s) {
+  if constexpr (MODE == kFwdC) return launch_grouped<MODE, FMT, THIN, SQ_CFG_GROUPED_FWDC>(gg, p, n, s);
+  else if constexpr (MODE == kDx) {
+    if (tokens <= 96 * others) return launch_grouped<MODE, FMT, THIN, SQ_CFG_GROUPED_THIN>(gg, p, n, s);
+    return dx_split_tails<FMT, THIN>(gg, p, n, s);
+  } else return launch_grouped<MODE, FMT, THIN, SQ_CFG_SMALL>(gg, p, n, s);
+}
+
+template <int MODE, int FMT>
+static int grouped_thin(GemmGroup& gg, const ExpertProblem* p, int n, hipStream_t s) {
+  gg.count = n;
+  for (int e = 0; e < n; ++e) {
+    gg.T[e] = p[e].T;
+    gg.ws2[e] = FMT == kNV ? p[e].ws2 : 1.0f;
+  }
+  if constexpr (MODE == kDx) return thin_dx<FMT>(nullptr, &gg, s);
+  else return thin_fwd<FMT>(nullptr, &gg, s);
 }
 
 // The large tile when the experts' tiles fill the chip and an expert averages
@@ -1674,22 +1670,47 @@ static int dx_split_tails(GemmGroup& gg, const ExpertProblem* p, int n, hipStrea
 template <int MODE, int FMT, int BM, int BN, int... REST>
 static int grouped_sized(GemmGroup& gg, const ExpertProblem* p, int n, hipStream_t s) {
   int64_t tokens = 0, big = 0;
+  int thin = 0;
   for (int e = 0; e < n; ++e) {
+    if (MODE != kDs && thin_takes(p[e].T, gg.base.K)) {
+      ++thin;
+      continue;
+    }
     tokens += p[e].T;
     const int M = MODE == kDs ? gg.base.M : p[e].T;
     big += (int64_t)((M + BM - 1) / BM) * ((gg.base.N + BN - 1) / BN);
   }
-  const bool large = big >= kCUs && tokens >= (int64_t)512 * n;
-  if (large) return launch_grouped<MODE, FMT, BM, BN, REST...>(gg, p, n, s);
-  if constexpr (MODE == kFwdC) {
-    if (tokens >= (int64_t)2048 * n) return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_FWDC_LONG>(gg, p, n, s);
-    return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_FWDC>(gg, p, n, s);
+  const int64_t others = n - thin;
+  const bool large = big >= kCUs && tokens >= 512 * others;
+  if constexpr (MODE == kDs) {
+    if (large) return launch_grouped<MODE, FMT, false, BM, BN, REST...>(gg, p, n, s);
+    return launch_ds_stream<FMT, SQ_CFG_DS_STREAM>(gg, p, n, s);
+  } else {
+    if (others == 0) return grouped_thin<MODE, FMT>(gg, p, n, s);
+    const bool longs = MODE == kFwdC && tokens >= 2048 * others;
+    if (!large && !longs)
+      return thin ? grouped_small<MODE, FMT, true>(gg, p, n, tokens, others, s)
+                  : grouped_small<MODE, FMT, false>(gg, p, n, tokens, others, s);
+    // large tiles for the others, a launch of their own for the few-token ones
+    ExpertProblem sub[kGroupMax];
+    if (thin) {
+      int m = 0;
+      for (int e = 0; e < n; ++e)
+        if (thin_takes(p[e].T, gg.base.K)) sub[m++] = p[e];
+      if (!set_experts(gg, sub, m, false)) return -1;     // a part of a set that fits
+      const int rc = grouped_thin<MODE, FMT>(gg, sub, m, s);
+      if (rc != 0) return rc;
+      m = 0;
+      for (int e = 0; e < n; ++e)
+        if (!thin_takes(p[e].T, gg.base.K)) sub[m++] = p[e];
+      if (!set_experts(gg, sub, m, false)) return -1;
+      p = sub;
+      n = m;
+    }
+    if (large) return launch_grouped<MODE, FMT, false, BM, BN, REST...>(gg, p, n, s);
+    if constexpr (MODE == kFwdC) return launch_grouped<MODE, FMT, false, SQ_CFG_GROUPED_FWDC_LONG>(gg, p, n, s);
+    return -1;                                            // not reached: `longs` is the register forward's
   }
-  else if constexpr (MODE == kDs) return launch_ds_stream<FMT, SQ_CFG_DS_STREAM>(gg, p, n, s);
-  else if constexpr (MODE == kDx) {
-    if (tokens <= (int64_t)96 * n) return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_THIN>(gg, p, n, s);
-    return dx_split_tails<FMT>(gg, p, n, s);
-  } else return launch_grouped<MODE, FMT, SQ_CFG_SMALL>(gg, p, n, s);
 }
 
 template <int MODE>
