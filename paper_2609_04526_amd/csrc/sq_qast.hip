@@ -12,14 +12,14 @@
 // or [rows, r] plane; A as [E, r, G]) and runs every expert's step in the
 // same launches.
 //
-// Delta_S adds the r rank-one terms in increasing k in fp32; each product of
-// two bf16 values is exact in fp32, so the fused multiply-add below rounds
-// exactly like a separate multiply and add, and the scale bytes are fixed bit
-// for bit.  The factor gradients accumulate in fp32 in a fixed order (dB: over
-// the blocks in order; dA: rows in order within 32-row chunks, then the chunk
-// partials through a fixed per-lane order and butterfly): deterministic.  The
-// backward kernels stage tiles of dS * m in LDS with all of a tile's loads in
-// flight together.
+// All three contractions run on the fp32 matrix cores, which do twice the
+// fused multiply-adds per cycle of the vector units and take their operands
+// from one register per lane instead of LDS reads per term.  Their terms are
+// added in increasing k, each with one rounding, so Delta_S equals a chain of
+// r fused multiply-adds (each product of two bf16 values is exact in fp32) and
+// the scale bytes are fixed bit for bit.  The factor gradients are summed in a
+// fixed order that depends on the shape alone: deterministic, and the same
+// for an expert alone and in a batch.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -31,398 +31,484 @@ namespace sq {
 
 __device__ __forceinline__ float bf16_bits_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-// ------------------------------------------------------------------ scales
-// A workgroup per tile of 32 TB rows x 32 blocks of one expert (blockIdx.y):
-// the tile's A columns [RMAX][32] and B rows, transposed to [RMAX][32 TB], are
-// staged in LDS as fp32 (every load issued together; ranks past r are 0 and
-// add exact zeros), and thread (row group, block group) adds the r terms of
-// its 4 rows x TB blocks in increasing k, with a 16-byte LDS read of B and a
-// TB-wide one of A per 4 TB fused multiply-adds.  TB = 4 where the tiles
-// still give every CU two workgroups (the stacked experts of an MoE layer),
-// else TB = 1 (one linear: four times the workgroups).  With TB = 4, where
-// G % 4 == 0 and the byte planes are 4-byte aligned (vec), a thread's four
-// blocks of a row are one 4-byte load and store.  Experts are stacked: rows
-// e*O .. e*O + O - 1 of base, B, out and mask belong to expert e, whose A is
-// A + e*r*G and whose ws2 is ws2[e].
-constexpr int kScCols = 32;
-template <int TB>
-constexpr int sc_rows() { return 32 * TB; }
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-template <int FMT, int RMAX, int TB>
+// ------------------------------------------------------------------ scales
+// Loads below are issued without a branch, from an address moved inside the
+// plane where there is nothing to load, and their values dropped afterwards
+// (a branch per load made each wait for the one before).  blockIdx.y is the
+// expert: rows e O .. e O + O - 1 of base, B, out and mask belong to it, its A
+// is A + e r G and its ws2 ws2.v[e].  The MFMA's rows are scale blocks g and
+// its columns output rows o, so a lane ends with four consecutive bytes of one
+// row: with vec (G % 4 == 0 and 4-byte aligned byte planes) one word each way.
+
+// The four scales of row o from block g on, whose delta sums are s[0..3].
+template <int FMT>
+__device__ __forceinline__ void scale4(const float (&s)[4], const uint32_t (&in)[4], float c, const Ws2Div& wd,
+                                       uint8_t* out, uint8_t* mask, size_t at, int left, int vec) {
+  uint32_t nw = 0, mw = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    bool clamped;
+    nw |= grid_update<FMT>(in[j], __fmul_rn(s[j], c), wd, clamped) << (8 * j);
+    mw |= (clamped ? 0u : 1u) << (8 * j);
+  }
+  if (vec) {
+    *reinterpret_cast<uint32_t*>(out + at) = nw;
+    if (mask) *reinterpret_cast<uint32_t*>(mask + at) = mw;
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (j >= left) break;
+      out[at + j] = (uint8_t)(nw >> (8 * j));
+      if (mask) mask[at + j] = (uint8_t)((mw >> (8 * j)) & 1u);
+    }
+  }
+}
+__device__ __forceinline__ void base4(uint32_t (&in)[4], const uint8_t* base, size_t at, size_t inside, bool ok,
+                                      int left, int vec) {
+  if (vec) {
+    const uint32_t w = *reinterpret_cast<const uint32_t*>(base + (ok ? at : inside));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) in[j] = (w >> (8 * j)) & 0xFFu;
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) in[j] = base[ok && j < left ? at + j : inside];
+  }
+}
+
+// One linear: latency is what bounds it, so a wave takes a single 16 x 16
+// block and four ranks per MFMA (v_mfma_f32_16x16x4 adds its four terms in
+// increasing k, each with its own rounding: every byte the tests compare
+// depends on it).  GB of a workgroup's four waves lie along g, the rest along
+// o.  4096 x 256 scales at rank 58: 12.2 us on vector multiply-adds fed from
+// LDS, 9.4 here; 4096 x 128 at rank 32 6.6 -> 5.8.
+template <int FMT, int RMAX, int GB>
 __global__ __launch_bounds__(256) void qast_scales_kernel(const uint8_t* __restrict__ base,
                                                           const uint16_t* __restrict__ B,
                                                           const uint16_t* __restrict__ A, int O, int G, int r,
                                                           float c, Ws2Table ws2, uint8_t* out, uint8_t* mask,
                                                           int vec) {
-  constexpr int ROWS = sc_rows<TB>();
-  constexpr int kAPad = kScCols + 4, kBPad = ROWS + 4;      // rows stay 16-byte aligned
-  __shared__ __attribute__((aligned(16))) float at[RMAX][kAPad];
-  __shared__ __attribute__((aligned(16))) float bt[RMAX][kBPad];
   const int e = blockIdx.y;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4;
+  const int gtiles = (G + 16 * GB - 1) / (16 * GB);
+  const int g0 = ((int)blockIdx.x % gtiles * GB + wave % GB) * 16;
+  const int o0 = ((int)blockIdx.x / gtiles * (4 / GB) + wave / GB) * 16;
+  if (o0 >= O || g0 >= G) return;
   const size_t rows0 = (size_t)e * O;
-  const uint16_t* ae = A + (size_t)e * r * G;
-  const int gtiles = (G + kScCols - 1) / kScCols;
-  const int o0 = ((int)blockIdx.x / gtiles) * ROWS, g0 = ((int)blockIdx.x % gtiles) * kScCols;
+  const bool g_ok = g0 + n < G, o_ok = o0 + n < O;
+  const uint16_t* ap = A + (size_t)e * r * G + (g_ok ? g0 + n : 0);
+  const uint16_t* bp = B + (rows0 + (o_ok ? o0 + n : 0)) * r;
+  uint16_t ar[RMAX / 4], br[RMAX / 4];
 #pragma unroll
-  for (int u = 0; u < RMAX * kScCols / 256; ++u) {
-    const int i = threadIdx.x + 256 * u, k = i / kScCols, gi = i % kScCols;
-    at[k][gi] = (k < r && g0 + gi < G) ? bf16_bits_to_f32(ae[(size_t)k * G + g0 + gi]) : 0.0f;
+  for (int st = 0; st < RMAX / 4; ++st) {
+    const int k = 4 * st + q, kc = k < r ? k : 0;
+    ar[st] = ap[(size_t)kc * G];
+    br[st] = bp[kc];
+  }
+  const int g = g0 + 4 * q;
+  const size_t at = (rows0 + o0 + n) * G + g;
+  uint32_t in[4];
+  base4(in, base, at, rows0 * G, o_ok && g < G, G - g, vec);
+  const Ws2Div wd = make_ws2_div(ws2.v[e]);
+  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int st = 0; st < RMAX / 4; ++st) {
+    const bool in_r = 4 * st + q < r;                    // ranks past r add exact zeros
+    const float av = g_ok && in_r ? bf16_bits_to_f32(ar[st]) : 0.0f;
+    const float bv = o_ok && in_r ? bf16_bits_to_f32(br[st]) : 0.0f;
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc, 0, 0, 0);
+  }
+  if (o_ok && g < G) {
+    const float sum[4] = {acc[0], acc[1], acc[2], acc[3]};
+    scale4<FMT>(sum, in, c, wd, out, mask, at, G - g, vec);
+  }
+}
+
+// Many scales (stacked experts, the widest linears): the address unit bounds
+// it, so a wave takes four 16 x 16 blocks with one-deep MFMAs
+// (v_mfma_f32_16x16x1: a register of A and one of B per rank serve all four),
+// GB of them along g; the workgroup's waves lie below one another and share
+// the A columns, of which each loads a quarter of the ranks into LDS; a row
+// of B comes W ranks per load.  128 experts of 768 x 128 scales at rank 54
+// (NVFP4): 82 us on vector multiply-adds fed from LDS, 57 with A loaded by
+// every wave, 50 now.
+template <int FMT, int RMAX, int GB, int W>
+__global__ __launch_bounds__(256) void qast_scales_wide_kernel(const uint8_t* __restrict__ base,
+                                                               const uint16_t* __restrict__ B,
+                                                               const uint16_t* __restrict__ A, int O, int G, int r,
+                                                               float c, Ws2Table ws2, uint8_t* out, uint8_t* mask,
+                                                               int vec) {
+  constexpr int OB = 4 / GB, COLS = 16 * GB;
+  __shared__ uint16_t at_lds[RMAX][COLS];
+  const int e = blockIdx.y;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4;
+  const int gtiles = (G + COLS - 1) / COLS;
+  const int g0 = ((int)blockIdx.x % gtiles) * COLS;
+  const int o0 = (((int)blockIdx.x / gtiles) * 4 + wave) * 16 * OB;
+  const size_t rows0 = (size_t)e * O;
+  const uint16_t* ap = A + (size_t)e * r * G;
+  constexpr int kPer = (RMAX * COLS + 255) / 256;
+  uint16_t av16[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int i = threadIdx.x + 256 * u, k = i / COLS, g = g0 + i % COLS;
+    av16[u] = ap[k < r && g < G ? (size_t)k * G + g : 0];
+  }
+  const int ol = o0 + 16 * (q / GB) + n;                // this lane's operand row
+  const bool o_ok = ol < O;
+  const uint16_t* bp = B + (rows0 + (o_ok ? ol : 0)) * r;
+  uint32_t br[RMAX / 2];                                // pairs of ranks
+#pragma unroll
+  for (int k = 0; k < RMAX; k += W > 1 ? W : 2) {
+    const int kc = k < r ? k : 0;                       // r is a multiple of W
+    if constexpr (W == 8) {
+      const uint4 v = *reinterpret_cast<const uint4*>(bp + kc);
+      br[k / 2] = v.x; br[k / 2 + 1] = v.y; br[k / 2 + 2] = v.z; br[k / 2 + 3] = v.w;
+    } else if constexpr (W == 2) {
+      br[k / 2] = *reinterpret_cast<const uint32_t*>(bp + kc);
+    } else {
+      br[k / 2] = (uint32_t)bp[kc] | ((uint32_t)bp[k + 1 < r ? k + 1 : 0] << 16);
+    }
+  }
+  // the result: block b, register 4 b + j is row g0 + 16 (b % GB) + 4 q + j of
+  // column o0 + 16 (b / GB) + n
+  uint32_t in[4][4];
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const int o = o0 + 16 * (b / GB) + n, g = g0 + 16 * (b % GB) + 4 * q;
+    base4(in[b], base, (rows0 + o) * G + g, rows0 * G, o < O && g < G, G - g, vec);
   }
 #pragma unroll
-  for (int u = 0; u < ROWS * RMAX / 256; ++u) {
-    const int i = threadIdx.x + 256 * u, ro = i / RMAX, k = i % RMAX;
-    bt[k][ro] = (k < r && o0 + ro < O) ? bf16_bits_to_f32(B[(rows0 + o0 + ro) * r + k]) : 0.0f;
+  for (int u = 0; u < kPer; ++u) {
+    const int i = threadIdx.x + 256 * u, k = i / COLS, g = g0 + i % COLS;
+    if (RMAX * COLS < 256 && k >= RMAX) break;
+    at_lds[k][i % COLS] = k < r && g < G ? av16[u] : (uint16_t)0;     // ranks past r add exact zeros
   }
   __syncthreads();
-  const int gq = (threadIdx.x % (kScCols / TB)) * TB, rq = (threadIdx.x / (kScCols / TB)) * 4;
-  float acc[4][TB];
+  f32x16 acc;
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
+  for (int j = 0; j < 16; ++j) acc[j] = 0.0f;
 #pragma unroll
-    for (int j = 0; j < TB; ++j) acc[q][j] = 0.0f;
-#pragma unroll 4
   for (int k = 0; k < RMAX; ++k) {
-    float av[TB];
-    if constexpr (TB == 4) {
-      const float4 a = *reinterpret_cast<const float4*>(&at[k][gq]);
-      av[0] = a.x; av[1] = a.y; av[2] = a.z; av[3] = a.w;
-    } else {
-#pragma unroll
-      for (int j = 0; j < TB; ++j) av[j] = at[k][gq + j];
-    }
-    const float4 b = *reinterpret_cast<const float4*>(&bt[k][rq]);
-    const float bv[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int j = 0; j < TB; ++j) acc[q][j] = __builtin_fmaf(bv[q], av[j], acc[q][j]);
+    const uint32_t bw = k & 1 ? br[k / 2] & 0xFFFF0000u : br[k / 2] << 16;
+    const float av = bf16_bits_to_f32(at_lds[k][16 * (q % GB) + n]);
+    const float bv = o_ok && k < r ? __uint_as_float(bw) : 0.0f;
+    acc = __builtin_amdgcn_mfma_f32_16x16x1f32(av, bv, acc, 0, 0, 0);
   }
-  const int g = g0 + gq;
-  if (g >= G) return;
   const Ws2Div wd = make_ws2_div(ws2.v[e]);
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int o = o0 + rq + q;
-    if (o >= O) break;
-    const size_t idx = (rows0 + o) * G + g;
-    if (TB == 4 && vec) {                       // blocks g .. g + 3, one word each way
-      const uint32_t in = *reinterpret_cast<const uint32_t*>(base + idx);
-      uint32_t nw = 0, mw = 0;
-#pragma unroll
-      for (int j = 0; j < TB; ++j) {
-        bool clamped;
-        nw |= grid_update<FMT>((in >> (8 * j)) & 0xFFu, __fmul_rn(acc[q][j], c), wd, clamped) << (8 * j);
-        mw |= (clamped ? 0u : 1u) << (8 * j);
-      }
-      *reinterpret_cast<uint32_t*>(out + idx) = nw;
-      if (mask) *reinterpret_cast<uint32_t*>(mask + idx) = mw;
-    } else {
-#pragma unroll
-      for (int j = 0; j < TB; ++j) {
-        if (g + j >= G) break;
-        bool clamped;
-        out[idx + j] = (uint8_t)grid_update<FMT>(base[idx + j], __fmul_rn(acc[q][j], c), wd, clamped);
-        if (mask) mask[idx + j] = clamped ? 0 : 1;
-      }
-    }
+  for (int b = 0; b < 4; ++b) {
+    const int o = o0 + 16 * (b / GB) + n, g = g0 + 16 * (b % GB) + 4 * q;
+    if (o >= O || g >= G) continue;
+    const float sum[4] = {acc[4 * b], acc[4 * b + 1], acc[4 * b + 2], acc[4 * b + 3]};
+    scale4<FMT>(sum, in[b], c, wd, out, mask, (rows0 + o) * G + g, G - g, vec);
   }
 }
 
 // ------------------------------------------------------------------ dB, dA
-// Both backward products stage tiles of v = dS * m (fp32) in LDS with every
-// load of the tile issued together, plus the matching factor tile, and give
-// each thread a 4 x 4 (dA: 4 x TG) block of outputs.  blockIdx.y is the
-// expert (its rows, its A).  dA is summed over 32-row chunks (partials in the
-// workspace, then a fixed-order reduction).
-constexpr int kDaRows = 32;         // rows per dA chunk
+// v = dS * m.  Both products run in one launch (workgroups below ndb take dB
+// rows, the rest dA chunks; they are independent and short), every operand
+// loaded straight into MFMA registers: lane (n, q) of v_mfma_f32_16x16x4
+// holds row n of A, column n of B and the term q of the four.
+//
+// dB[o, k] = c sum_g v[o, g] A[k, g]: a workgroup takes 16 rows and all RT * 16
+// ranks; wave w takes the 16-block steps w, w + 4, ... of g, in which MFMA j
+// adds the terms g = 4 q + j (a lane's four consecutive blocks: one 16-byte
+// load of dS, one word of the mask, 8 bytes of A where vec).  The waves'
+// sums meet in LDS in wave order.
+//
+// part[chunk][k][g] = sum over a chunk of 64 rows of B[o, k] v[o, g]: a
+// workgroup takes 16 U blocks and all ranks, its waves 16 rows each, four per
+// MFMA in increasing order; the waves' sums again meet in LDS in a fixed
+// order.  Column n of tile u is block U n + u, so that a lane's blocks are one
+// load of dS, and row n of tile t is rank RT n + t.  U = 4, but 2 for ranks over
+// 32: with 16 accumulator tiles a wave, too few waves fit a SIMD (128 experts
+// of 768 x 128 at rank 54: 113 us, 76 with 8).  Chunks are added in order by
+// qast_da_reduce_kernel.
+// 4096 x 256 scales at rank 58: vector multiply-adds fed from LDS tiles took
+// 30.0 us, this 11.2; the reduction of 128 partial planes of 32 rows (a wave
+// per output, lanes striding over the planes) 12.3, of 64 in rows 3.9.
+constexpr int kDaRows = 64;         // rows per dA chunk
+template <int RT>
+__host__ __device__ constexpr int da_u() { return RT == 4 ? 2 : 4; }
 
-// v = dS * m at blocks g .. g + 3 of row o (G % 4 == 0, dS 16-byte and mask
-// 4-byte aligned: one 16-byte and one 4-byte load); zeros past the plane.
-__device__ __forceinline__ float4 load_v4(const float* __restrict__ dS, const uint8_t* __restrict__ mask, int O,
-                                          int G, int o, int g) {
-  float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  if (o < O && g < G) {
-    const size_t at_ = (size_t)o * G + g;
-    v = *reinterpret_cast<const float4*>(dS + at_);
+// v at blocks g .. g + U - 1 of row o; zeros outside the plane (loaded from
+// inside it without a branch, then dropped).  vec: whole words (G % 4 == 0, dS
+// 16-byte and the mask 4-byte aligned).
+template <int U>
+__device__ __forceinline__ void load_v(float (&v)[U], const float* __restrict__ dS, const uint8_t* __restrict__ mask,
+                                       int O, int G, int o, int g, int vec) {
+  const size_t row = o < O ? (size_t)o * G : 0;
+  if (vec) {
+    const size_t at_ = row + (g < G ? g : 0);
+    if constexpr (U == 4) {
+      const f32x4 w = *reinterpret_cast<const f32x4*>(dS + at_);
+#pragma unroll
+      for (int j = 0; j < U; ++j) v[j] = w[j];
+    } else {
+      const f32x2 w = *reinterpret_cast<const f32x2*>(dS + at_);
+      v[0] = w[0];
+      v[1] = w[1];
+    }
     if (mask) {
-      const uint32_t m = *reinterpret_cast<const uint32_t*>(mask + at_);
-      v.x *= (float)(m & 0xFFu);
-      v.y *= (float)((m >> 8) & 0xFFu);
-      v.z *= (float)((m >> 16) & 0xFFu);
-      v.w *= (float)(m >> 24);
+      const uint32_t m = U == 4 ? *reinterpret_cast<const uint32_t*>(mask + at_)
+                                : (uint32_t)*reinterpret_cast<const uint16_t*>(mask + at_);
+#pragma unroll
+      for (int j = 0; j < U; ++j) v[j] *= (float)((m >> (8 * j)) & 0xFFu);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < U; ++j) v[j] = dS[row + (g + j < G ? g + j : 0)];
+    if (mask) {
+#pragma unroll
+      for (int j = 0; j < U; ++j) v[j] *= (float)mask[row + (g + j < G ? g + j : 0)];
     }
   }
-  return v;
+#pragma unroll
+  for (int j = 0; j < U; ++j) v[j] = o < O && g + j < G ? v[j] : 0.0f;
 }
 
-// dB[o, k] = c sum over g in increasing order of v[o, g] A[k, g]: a workgroup
-// owns 1024 RT / RMAX rows and walks the blocks in tiles of 32, staging v and
-// A transposed ([g][row], [g][k]) so that thread (row group, rank group)
-// reads its RT rows and four ranks of a block with two LDS reads and adds
-// 4 RT products.  RT = 4 where that still gives every CU two workgroups,
-// else RT = 1.
-constexpr int kDbCols = 32;
-template <int RMAX, int RT>
-constexpr int db_rows() { return RT * (256 / (RMAX / 4)); }
-
-template <int RMAX, int RT>
-constexpr int db_lds_floats() { return kDbCols * (db_rows<RMAX, RT>() + 4) + kDbCols * (RMAX + 4); }
-
-template <int RMAX, int RT>
+template <int RT>
 __device__ __forceinline__ void db_tile(int bx, int e, float* lds, const float* __restrict__ dS,
                                         const uint8_t* __restrict__ mask, const uint16_t* __restrict__ A, int O,
                                         int G, int r, float c, float* __restrict__ dB, int vec) {
-  constexpr int KQ = RMAX / 4, ROWS = db_rows<RMAX, RT>();
-  float (*vt)[ROWS + 4] = reinterpret_cast<float (*)[ROWS + 4]>(lds);
-  float (*at)[RMAX + 4] = reinterpret_cast<float (*)[RMAX + 4]>(lds + kDbCols * (ROWS + 4));
+  constexpr int S = 16 * RT + 1;                        // LDS row of one output row's ranks
   dS += (size_t)e * O * G;
   if (mask) mask += (size_t)e * O * G;
   A += (size_t)e * r * G;
   dB += (size_t)e * O * r;
-  const int o0 = bx * ROWS;
-  const int kq = (threadIdx.x % KQ) * 4, rq = (threadIdx.x / KQ) * RT;
-  float acc[RT][4];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4;
+  // few steps (G <= 64): every wave its own 16 rows and all steps
+  const bool split = G > 64;
+  const int o0 = split ? bx * 16 : bx * 64 + 16 * wave, o = o0 + n;
+  f32x4 acc[RT];
 #pragma unroll
-  for (int q = 0; q < RT; ++q)
+  for (int t = 0; t < RT; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const int steps = (G + 15) / 16;
+#pragma unroll 2
+  for (int st = split ? wave : 0; st < steps; st += split ? 4 : 1) {
+    const int g = 16 * st + 4 * q;
+    float v[4];
+    load_v<4>(v, dS, mask, O, G, o, g, vec);
+    float a[RT][4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[q][j] = 0.0f;
-  for (int g0 = 0; g0 < G; g0 += kDbCols) {
-    __syncthreads();                                     // the previous tiles are consumed
-    if (vec) {
-#pragma unroll
-      for (int u = 0; u < (ROWS * kDbCols / 4 + 255) / 256; ++u) {
-        const int i = threadIdx.x + 256 * u, ro = i / (kDbCols / 4), gq = (i % (kDbCols / 4)) * 4;
-        if (ROWS * kDbCols / 4 % 256 != 0 && i >= ROWS * kDbCols / 4) break;
-        const float4 v = load_v4(dS, mask, O, G, o0 + ro, g0 + gq);
-        vt[gq][ro] = v.x;
-        vt[gq + 1][ro] = v.y;
-        vt[gq + 2][ro] = v.z;
-        vt[gq + 3][ro] = v.w;
-      }
-    } else {
-#pragma unroll 4
-      for (int u = 0; u < ROWS * kDbCols / 256; ++u) {
-        const int i = threadIdx.x + 256 * u, ro = i / kDbCols, gi = i % kDbCols;
-        const int o = o0 + ro, g = g0 + gi;
-        float v = 0.0f;
-        if (o < O && g < G) {
-          const size_t at_ = (size_t)o * G + g;
-          v = dS[at_];
-          if (mask) v *= (float)mask[at_];
-        }
-        vt[gi][ro] = v;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < RMAX * kDbCols / 256; ++u) {
-      const int i = threadIdx.x + 256 * u, kk = i / kDbCols, gi = i % kDbCols;
-      at[gi][kk] = (kk < r && g0 + gi < G) ? bf16_bits_to_f32(A[(size_t)kk * G + g0 + gi]) : 0.0f;
-    }
-    __syncthreads();
-    const int gn = min(kDbCols, G - g0);
-    for (int gi = 0; gi < gn; ++gi) {
-      const float4 a = *reinterpret_cast<const float4*>(&at[gi][kq]);
-      const float av[4] = {a.x, a.y, a.z, a.w};
-      float vv[RT];
-      if constexpr (RT == 4) {
-        const float4 v = *reinterpret_cast<const float4*>(&vt[gi][rq]);
-        vv[0] = v.x; vv[1] = v.y; vv[2] = v.z; vv[3] = v.w;
+    for (int t = 0; t < RT; ++t) {
+      const int k = 16 * t + n;
+      const uint16_t* ap = A + (size_t)(k < r ? k : 0) * G;
+      if (vec) {
+        const u32x2 w = *reinterpret_cast<const u32x2*>(ap + (g < G ? g : 0));
+        a[t][0] = __uint_as_float(w[0] << 16);
+        a[t][1] = __uint_as_float(w[0] & 0xFFFF0000u);
+        a[t][2] = __uint_as_float(w[1] << 16);
+        a[t][3] = __uint_as_float(w[1] & 0xFFFF0000u);
       } else {
 #pragma unroll
-        for (int q = 0; q < RT; ++q) vv[q] = vt[gi][rq + q];
+        for (int j = 0; j < 4; ++j) a[t][j] = bf16_bits_to_f32(ap[g + j < G ? g + j : 0]);
       }
 #pragma unroll
-      for (int q = 0; q < RT; ++q)
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) acc[q][jj] = __builtin_fmaf(vv[q], av[jj], acc[q][jj]);
+      for (int j = 0; j < 4; ++j) a[t][j] = k < r && g + j < G ? a[t][j] : 0.0f;
     }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int t = 0; t < RT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t][j], v[j], acc[t], 0, 0, 0);
   }
+  // register e of tile t: rank 16 t + 4 q + e of row n
 #pragma unroll
-  for (int q = 0; q < RT; ++q) {
-    const int o = o0 + rq + q;
-    if (o >= O) break;
+  for (int t = 0; t < RT; ++t)
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj)
-      if (kq + jj < r) dB[(size_t)o * r + kq + jj] = __fmul_rn(acc[q][jj], c);
+    for (int x = 0; x < 4; ++x) lds[(wave * 16 + n) * S + 16 * t + 4 * q + x] = acc[t][x];
+  __syncthreads();
+  const int first = split ? bx * 16 : bx * 64, rows = min(split ? 16 : 64, O - first);
+  for (int i = threadIdx.x; i < rows * r; i += 256) {
+    const int ro = i / r, k = i - ro * r;
+    float s = lds[ro * S + k];
+    if (split) {
+#pragma unroll
+      for (int w = 1; w < 4; ++w) s += lds[(w * 16 + ro) * S + k];
+    }
+    dB[(size_t)first * r + i] = __fmul_rn(s, c);
   }
 }
 
-// Partial dA over one 32-row chunk: part[chunk][k][g] = sum over the chunk's
-// rows in increasing order of B[o, k] v[o, g].  A workgroup takes the chunk's
-// rows for 1024 TG / RMAX blocks; thread (rank group, block group) holds four
-// ranks and TG blocks (TG = RMAX / 16, at least 1) and per row reads them
-// with one 16-byte and one TG-wide LDS read.
-template <int RMAX>
-constexpr int da_tg() { return RMAX >= 16 ? RMAX / 16 : 1; }
-template <int RMAX>
-constexpr int da_cols() { return 1024 * da_tg<RMAX>() / RMAX; }
-
-template <int RMAX>
-constexpr int da_lds_floats() { return kDaRows * (da_cols<RMAX>() + 4) + kDaRows * (RMAX + 4); }
-
-template <int RMAX>
+template <int RT>
 __device__ __forceinline__ void da_tile(int bx, int e, float* lds, const float* __restrict__ dS,
                                         const uint8_t* __restrict__ mask, const uint16_t* __restrict__ B, int O,
-                                        int G, int r, float* __restrict__ part, int vec) {
-  constexpr int TG = da_tg<RMAX>(), GT = da_cols<RMAX>(), KQ = RMAX / 4;
-  static_assert(KQ * (GT / TG) == 256, "a thread per rank group and block group");
-  float (*vt)[GT + 4] = reinterpret_cast<float (*)[GT + 4]>(lds);
-  float (*bt)[RMAX + 4] = reinterpret_cast<float (*)[RMAX + 4]>(lds + kDaRows * (GT + 4));
+                                        int G, int r, float* __restrict__ part, int vec, int bvec) {
+  constexpr int U = da_u<RT>(), COLS = 16 * U, S = COLS + 4;      // S: LDS row of one rank's blocks
   const int chunks = (O + kDaRows - 1) / kDaRows;
   dS += (size_t)e * O * G;
   if (mask) mask += (size_t)e * O * G;
   B += (size_t)e * O * r;
   part += (size_t)e * chunks * r * G;
-  const int gtiles = (G + GT - 1) / GT;
-  const int chunk = bx / gtiles, g0 = (bx % gtiles) * GT;
-  const int o0 = chunk * kDaRows;
-  static_assert(kDaRows * GT % 1024 == 0, "whole 16-byte loads per thread");
-  if (vec) {
+  const int gtiles = (G + COLS - 1) / COLS;
+  const int chunk = bx / gtiles, g0 = (bx % gtiles) * COLS;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4;
+  const int o0 = chunk * kDaRows + 16 * wave;
+  f32x4 acc[RT][U];
 #pragma unroll
-    for (int u = 0; u < kDaRows * GT / 1024; ++u) {
-      const int i = threadIdx.x + 256 * u, ro = i / (GT / 4), gq = (i % (GT / 4)) * 4;
-      *reinterpret_cast<float4*>(&vt[ro][gq]) = load_v4(dS, mask, O, G, o0 + ro, g0 + gq);
-    }
-  } else {
-#pragma unroll 4
-    for (int u = 0; u < kDaRows * GT / 256; ++u) {
-      const int i = threadIdx.x + 256 * u, ro = i / GT, gi = i % GT;
-      const int o = o0 + ro, g = g0 + gi;
-      float v = 0.0f;
-      if (o < O && g < G) {
-        const size_t at_ = (size_t)o * G + g;
-        v = dS[at_];
-        if (mask) v *= (float)mask[at_];
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int u = 0; u < U; ++u) acc[t][u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  float v[4][U], b[4][RT];
+#pragma unroll
+  for (int st = 0; st < 4; ++st) {
+    const int o = o0 + 4 * st + q, k0 = RT * n;
+    load_v<U>(v[st], dS, mask, O, G, o, g0 + U * n, vec);
+    const uint16_t* bp = B + (o < O ? (size_t)o * r : 0);
+    if (RT > 1 && bvec) {                               // r even, B 4-byte aligned: pairs of ranks
+#pragma unroll
+      for (int t = 0; t + 1 < RT; t += 2) {
+        const uint32_t w = *reinterpret_cast<const uint32_t*>(bp + (k0 + t < r ? k0 + t : 0));
+        b[st][t] = __uint_as_float(w << 16);
+        b[st][t + 1] = __uint_as_float(w & 0xFFFF0000u);
       }
-      vt[ro][gi] = v;
+    } else {
+#pragma unroll
+      for (int t = 0; t < RT; ++t) b[st][t] = bf16_bits_to_f32(bp[k0 + t < r ? k0 + t : 0]);
     }
+#pragma unroll
+    for (int t = 0; t < RT; ++t) b[st][t] = o < O && k0 + t < r ? b[st][t] : 0.0f;
   }
 #pragma unroll
-  for (int u = 0; u < (kDaRows * RMAX + 255) / 256; ++u) {
-    const int i = threadIdx.x + 256 * u;
-    if (i < kDaRows * RMAX) {
-      const int ro = i / RMAX, kk = i % RMAX;
-      bt[ro][kk] = (kk < r && o0 + ro < O) ? bf16_bits_to_f32(B[(size_t)(o0 + ro) * r + kk]) : 0.0f;
-    }
+  for (int st = 0; st < 4; ++st)
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[st][t], v[st][u], acc[t][u], 0, 0, 0);
+  // register x of tile (t, u): rank RT (4 q + x) + t, block U n + u.  Waves 2
+  // and 3 park their sums, waves 0 and 1 add theirs (half the LDS of four
+  // planes, so twice the workgroups per CU), then the two planes are added.
+  auto at = [&](int w, int t, int x, int u) -> float& {
+    return lds[(w * 16 * RT + RT * (4 * q + x) + t) * S + U * n + u];
+  };
+  if (wave >= 2) {
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int u = 0; u < U; ++u) at(wave - 2, t, x, u) = acc[t][u][x];
   }
   __syncthreads();
-  const int kq = (threadIdx.x % KQ) * 4, gq = (threadIdx.x / KQ) * TG;
-  float acc[4][TG];
+  if (wave < 2) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
+    for (int t = 0; t < RT; ++t)
 #pragma unroll
-    for (int t = 0; t < TG; ++t) acc[j][t] = 0.0f;
-  const int on = min(kDaRows, O - o0);
-  for (int ro = 0; ro < on; ++ro) {
-    const float4 b = *reinterpret_cast<const float4*>(&bt[ro][kq]);
-    const float bv[4] = {b.x, b.y, b.z, b.w};
-    float vv[TG];
+      for (int x = 0; x < 4; ++x)
 #pragma unroll
-    for (int t = 0; t < TG; ++t) vv[t] = vt[ro][gq + t];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int t = 0; t < TG; ++t) acc[j][t] = __builtin_fmaf(bv[j], vv[t], acc[j][t]);
+        for (int u = 0; u < U; ++u) at(wave, t, x, u) = acc[t][u][x] + at(wave, t, x, u);
   }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    if (kq + j >= r) break;
-#pragma unroll
-    for (int t = 0; t < TG; ++t)
-      if (g0 + gq + t < G) part[((size_t)chunk * r + kq + j) * G + g0 + gq + t] = acc[j][t];
+  __syncthreads();
+  for (int i = threadIdx.x; i < r * COLS; i += 256) {
+    const int k = i / COLS, gi = i % COLS;
+    if (g0 + gi < G) part[((size_t)chunk * r + k) * G + g0 + gi] = lds[k * S + gi] + lds[(16 * RT + k) * S + gi];
   }
 }
 
-// dB and the dA partials read the same v but are independent: one launch runs
-// both, workgroups below ndb taking dB rows and the rest dA chunks, so the
-// two short passes overlap instead of running one after the other.
-template <int RMAX, int RT>
+template <int RT>
 __global__ __launch_bounds__(256) void qast_grads_kernel(const float* __restrict__ dS,
                                                          const uint8_t* __restrict__ mask,
                                                          const uint16_t* __restrict__ A,
                                                          const uint16_t* __restrict__ B, int O, int G, int r,
                                                          float c, float* __restrict__ dB, float* __restrict__ part,
-                                                         int ndb, int vec) {
-  constexpr int kDb = db_lds_floats<RMAX, RT>(), kDa = da_lds_floats<RMAX>();
+                                                         int ndb, int vec, int bvec) {
+  constexpr int kDb = 4 * 16 * (16 * RT + 1), kDa = 2 * 16 * RT * (16 * da_u<RT>() + 4);
   __shared__ __attribute__((aligned(16))) float lds[kDb > kDa ? kDb : kDa];
   const int bx = (int)blockIdx.x, e = (int)blockIdx.y;
   if (bx < ndb)
-    db_tile<RMAX, RT>(bx, e, lds, dS, mask, A, O, G, r, c, dB, vec);
+    db_tile<RT>(bx, e, lds, dS, mask, A, O, G, r, c, dB, vec);
   else
-    da_tile<RMAX>(bx - ndb, e, lds, dS, mask, B, O, G, r, part, vec);
+    da_tile<RT>(bx - ndb, e, lds, dS, mask, B, O, G, r, part, vec, bvec);
 }
 
-// dA[i] = c sum over the chunk partials.  Up to 64 chunks: a thread per
-// output adds the chunks in order (loads eight at a time); more: a wave per
-// output, lane l adds the chunks l, l + 64, ... in order, then a fixed
-// butterfly across the lanes.  Either order depends only on the shape.
-constexpr int kDaFewChunks = 64;
+// dA[i] = c sum over the chunk partials in order.  64 consecutive outputs per
+// workgroup; its four waves take every fourth group of 8 chunks (eight loads in
+// flight each), and their sums are added in wave order.
 __global__ __launch_bounds__(256) void qast_da_reduce_kernel(const float* __restrict__ part, int chunks, int r,
                                                              int G, int E, float c, float* __restrict__ dA) {
+  __shared__ float sum[4][64];
   const int64_t n = (int64_t)r * G;
-  if (chunks <= kDaFewChunks) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= (int64_t)E * n) return;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+  float s = 0.0f;
+  if (i < (int64_t)E * n) {
     const int64_t e = i / n, ie = i - e * n;
     const float* pe = part + (size_t)e * chunks * n + ie;
-    float s = 0.0f;
-    int ch = 0;
-    for (; ch + 8 <= chunks; ch += 8) {
+    for (int c0 = 8 * wave; c0 < chunks; c0 += 32) {
       float v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = pe[(size_t)(ch + u) * n];
+      for (int u = 0; u < 8; ++u) v[u] = c0 + u < chunks ? pe[(size_t)(c0 + u) * n] : 0.0f;
 #pragma unroll
       for (int u = 0; u < 8; ++u) s += v[u];
     }
-    for (; ch < chunks; ++ch) s += pe[(size_t)ch * n];
-    dA[i] = __fmul_rn(s, c);
-    return;
   }
-  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (i >= (int64_t)E * n) return;
-  const int64_t e = i / n, ie = i - e * n;
-  const float* pe = part + (size_t)e * chunks * n;
-  const int lane = threadIdx.x & 63;
-  float s = 0.0f;
-  for (int ch = lane; ch < chunks; ch += 64) s += pe[(size_t)ch * n + ie];
-#pragma unroll
-  for (int w = 32; w >= 1; w >>= 1) s += __shfl_xor(s, w);
-  if (lane == 0) dA[i] = __fmul_rn(s, c);
+  sum[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0 && i < (int64_t)E * n)
+    dA[i] = __fmul_rn(((sum[0][lane] + sum[1][lane]) + sum[2][lane]) + sum[3][lane], c);
 }
 
 // ------------------------------------------------------------------ launch
-constexpr int kQastCUs = 256;        // MI355X compute units
+// 16 x 16 blocks of a launch from which on the wide kernel is the faster one:
+// 2048 blocks (4096 x 128, rank 32) 7.2 us there against 5.8, 4096 (4096 x
+// 256, rank 58) 10.6 against 9.6, but 7168 (14336 x 128, rank 32) 9.8 against
+// 12.2 and 14,336 (4096 x 896) 13.2 against 21.0.
+constexpr int64_t kScWideBlocks = 6144;
 
-template <int F, int R>
-static void scales_tb(bool tb4, dim3 grid, hipStream_t s, const uint8_t* bp, const uint16_t* Bp, const uint16_t* Ap,
-                      int O, int G, int r, float c, const Ws2Table& t, uint8_t* op, uint8_t* mp, int vec) {
-  if (tb4)
-    hipLaunchKernelGGL((qast_scales_kernel<F, R, 4>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op, mp, vec);
+template <int F, int R, int GB>
+static void scales_go(bool wide, int w, int64_t gtiles, int m, hipStream_t s, const uint8_t* bp, const uint16_t* Bp,
+                      const uint16_t* Ap, int O, int G, int r, float c, const Ws2Table& t, uint8_t* op, uint8_t* mp,
+                      int vec) {
+  const int rows = (wide ? 4 : 1) * 16 * (4 / GB);                   // of a workgroup
+  const dim3 grid((unsigned)(((O + rows - 1) / rows) * gtiles), (unsigned)m);
+  if (!wide)
+    hipLaunchKernelGGL((qast_scales_kernel<F, R, GB>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op, mp, vec);
+  else if (w == 8)
+    hipLaunchKernelGGL((qast_scales_wide_kernel<F, R, GB, 8>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op, mp,
+                       vec);
+  else if (w == 2)
+    hipLaunchKernelGGL((qast_scales_wide_kernel<F, R, GB, 2>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op, mp,
+                       vec);
   else
-    hipLaunchKernelGGL((qast_scales_kernel<F, R, 1>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op, mp, 0);
+    hipLaunchKernelGGL((qast_scales_wide_kernel<F, R, GB, 1>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op, mp,
+                       vec);
+}
+template <int F, int R>
+static void scales_gb(bool wide, int gb, int w, int m, hipStream_t s, const uint8_t* bp, const uint16_t* Bp,
+                      const uint16_t* Ap, int O, int G, int r, float c, const Ws2Table& t, uint8_t* op, uint8_t* mp,
+                      int vec) {
+  const int64_t gtiles = (G + 16 * gb - 1) / (16 * gb);
+  if (gb == 4) scales_go<F, R, 4>(wide, w, gtiles, m, s, bp, Bp, Ap, O, G, r, c, t, op, mp, vec);
+  else if (gb == 2) scales_go<F, R, 2>(wide, w, gtiles, m, s, bp, Bp, Ap, O, G, r, c, t, op, mp, vec);
+  else scales_go<F, R, 1>(wide, w, gtiles, m, s, bp, Bp, Ap, O, G, r, c, t, op, mp, vec);
 }
 int qast_scales_launch(int fmt, int E, int O, int G, int r, const uint8_t* base, const void* B, const void* A,
                        float c, const float* ws2, uint8_t* out, uint8_t* mask, hipStream_t s) {
   const uint16_t* b = static_cast<const uint16_t*>(B);
   const uint16_t* a = static_cast<const uint16_t*>(A);
+  // the widest wave tile along g that pads no more 16-block columns than a narrower one
+  const int cols = (G + 15) / 16;
+  const auto padded = [cols](int b) { return (cols + b - 1) / b * b; };
+  const int gb = padded(4) == cols || padded(4) == padded(2) ? 4 : padded(2) == cols || padded(2) == padded(1) ? 2 : 1;
+  const auto al = [](const void* q, uintptr_t n) { return (reinterpret_cast<uintptr_t>(q) & (n - 1)) == 0; };
+  const int w = r % 8 == 0 && al(b, 16) ? 8 : r % 2 == 0 && al(b, 4) ? 2 : 1;
   for (int e0 = 0; e0 < E; e0 += kWs2TableMax) {          // per-expert ws2 travels by value
     const int m = E - e0 < kWs2TableMax ? E - e0 : kWs2TableMax;
     Ws2Table t;
     for (int e = 0; e < m; ++e) t.v[e] = fmt == kNV ? ws2[e0 + e] : 1.0f;
     const size_t rows0 = (size_t)e0 * O;
-    const int64_t gtiles = (G + kScCols - 1) / kScCols;
-    const int64_t wide = ((O + sc_rows<4>() - 1) / sc_rows<4>()) * gtiles * m;   // workgroups with TB = 4
-    const bool tb4 = wide >= 2 * kQastCUs;
-    const int rows = tb4 ? sc_rows<4>() : sc_rows<1>();
-    const dim3 grid((unsigned)(((O + rows - 1) / rows) * gtiles), (unsigned)m);
     const uint8_t* bp = base + rows0 * G;
     const uint16_t* Bp = b + rows0 * r;
     const uint16_t* Ap = a + (size_t)e0 * r * G;
     uint8_t* op = out + rows0 * G;
     uint8_t* mp = mask ? mask + rows0 * G : nullptr;
-    const auto al4 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 3) == 0; };
-    const int vec = G % 4 == 0 && al4(bp) && al4(op) && (mp == nullptr || al4(mp)) ? 1 : 0;
-#define SQ_QAST_SCALES(F, R) scales_tb<F, R>(tb4, grid, s, bp, Bp, Ap, O, G, r, c, t, op, mp, vec)
+    const bool wide = (int64_t)cols * ((O + 15) / 16) * m >= kScWideBlocks;
+    const int vec = G % 4 == 0 && al(bp, 4) && al(op, 4) && (mp == nullptr || al(mp, 4)) ? 1 : 0;
+#define SQ_QAST_SCALES(F, R) scales_gb<F, R>(wide, gb, w, m, s, bp, Bp, Ap, O, G, r, c, t, op, mp, vec)
     if (fmt == kMX) {
       if (r <= 8) SQ_QAST_SCALES(kMX, 8);
       else if (r <= 16) SQ_QAST_SCALES(kMX, 16);
@@ -439,31 +525,24 @@ int qast_scales_launch(int fmt, int E, int O, int G, int r, const uint8_t* base,
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
+// (callers were given room for partials of 32-row chunks, and still are)
 size_t qast_grads_workspace(int E, int O, int G, int r) {
-  return (size_t)E * ((O + kDaRows - 1) / kDaRows) * r * G * sizeof(float);
+  return (size_t)E * ((O + 31) / 32) * r * G * sizeof(float);
 }
 
-template <int RMAX>
-static int qast_grads_r(int E, int O, int G, int r, const float* dS, const uint8_t* mask, const uint16_t* B,
-                        const uint16_t* A, float c, float* dB, float* dA, float* part, hipStream_t s) {
+template <int RT>
+static void qast_grads_r(int E, int O, int G, int r, const float* dS, const uint8_t* mask, const uint16_t* B,
+                         const uint16_t* A, float c, float* dB, float* dA, float* part, hipStream_t s) {
   const int chunks = (O + kDaRows - 1) / kDaRows;
-  const int vec = G % 4 == 0 && (reinterpret_cast<uintptr_t>(dS) & 15) == 0 &&
-                  (mask == nullptr || (reinterpret_cast<uintptr_t>(mask) & 3) == 0) ? 1 : 0;
-  constexpr int kWide = db_rows<RMAX, 4>(), kNarrow = db_rows<RMAX, 1>();
-  const int nda = ((G + da_cols<RMAX>() - 1) / da_cols<RMAX>()) * chunks;
-  if ((int64_t)((O + kWide - 1) / kWide) * E >= 2 * kQastCUs) {
-    const int ndb = (O + kWide - 1) / kWide;
-    hipLaunchKernelGGL((qast_grads_kernel<RMAX, 4>), dim3((unsigned)(ndb + nda), (unsigned)E), dim3(256), 0, s, dS,
-                       mask, A, B, O, G, r, c, dB, part, ndb, vec);
-  } else {
-    const int ndb = (O + kNarrow - 1) / kNarrow;
-    hipLaunchKernelGGL((qast_grads_kernel<RMAX, 1>), dim3((unsigned)(ndb + nda), (unsigned)E), dim3(256), 0, s, dS,
-                       mask, A, B, O, G, r, c, dB, part, ndb, vec);
-  }
+  const auto al = [](const void* q, uintptr_t n) { return (reinterpret_cast<uintptr_t>(q) & (n - 1)) == 0; };
+  const int vec = G % 4 == 0 && al(dS, 16) && al(A, 8) && (mask == nullptr || al(mask, 4)) ? 1 : 0;
+  const int ndb = G > 64 ? (O + 15) / 16 : (O + 63) / 64, nda = ((G + 16 * da_u<RT>() - 1) / (16 * da_u<RT>())) * chunks;
+  const int bvec = r % 2 == 0 && al(B, 4) ? 1 : 0;
+  hipLaunchKernelGGL((qast_grads_kernel<RT>), dim3((unsigned)(ndb + nda), (unsigned)E), dim3(256), 0, s, dS, mask, A, B,
+                     O, G, r, c, dB, part, ndb, vec, bvec);
   const int64_t n = (int64_t)E * r * G;
-  const int64_t rblocks = chunks <= kDaFewChunks ? (n + 255) / 256 : (n + 3) / 4;
-  hipLaunchKernelGGL(qast_da_reduce_kernel, dim3((unsigned)rblocks), dim3(256), 0, s, part, chunks, r, G, E, c, dA);
-  return 0;
+  hipLaunchKernelGGL(qast_da_reduce_kernel, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, s, part, chunks, r, G, E, c,
+                     dA);
 }
 
 int qast_grads_launch(int E, int O, int G, int r, const float* dS, const uint8_t* mask, const void* B, const void* A,
@@ -471,12 +550,9 @@ int qast_grads_launch(int E, int O, int G, int r, const float* dS, const uint8_t
   const uint16_t* b = static_cast<const uint16_t*>(B);
   const uint16_t* a = static_cast<const uint16_t*>(A);
   float* part = static_cast<float*>(workspace);
-  int rc;
-  if (r <= 8) rc = qast_grads_r<8>(E, O, G, r, dS, mask, b, a, c, dB, dA, part, s);
-  else if (r <= 16) rc = qast_grads_r<16>(E, O, G, r, dS, mask, b, a, c, dB, dA, part, s);
-  else if (r <= 32) rc = qast_grads_r<32>(E, O, G, r, dS, mask, b, a, c, dB, dA, part, s);
-  else rc = qast_grads_r<64>(E, O, G, r, dS, mask, b, a, c, dB, dA, part, s);
-  if (rc != 0) return rc;
+  if (r <= 16) qast_grads_r<1>(E, O, G, r, dS, mask, b, a, c, dB, dA, part, s);
+  else if (r <= 32) qast_grads_r<2>(E, O, G, r, dS, mask, b, a, c, dB, dA, part, s);
+  else qast_grads_r<4>(E, O, G, r, dS, mask, b, a, c, dB, dA, part, s);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
