@@ -19,6 +19,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "sq_device.h"
 #include "sq_launch.h"
 #include "sq_rtn.h"
@@ -26,24 +28,35 @@
 namespace sq {
 
 // ------------------------------------------------------------ requant
-constexpr int kReqRows = 32;        // rows per workgroup: 4 waves x 8 rows
-constexpr int kReqRowsPerWave = 8;
-constexpr int kReqCols = 512;       // columns per workgroup: 64 lanes x 8
+// A wave takes 16 rows x 128 columns on v_mfma_f32_16x16x4_f32, whose four
+// terms are added in increasing k with one rounding each: S is the chain of r
+// fused multiply-adds (on exact products) that fixes the codes bit for bit.
+// The MFMA's rows are weight columns and its columns weight rows o; row m of
+// tile u is column 32 (m / 4) + 8 (m % 4) + u, so that lane (n, q) loads the
+// operands of all eight tiles as the 8 consecutive columns 8 n .. 8 n + 7 of A
+// (16 bytes, a whole 256-byte run per rank), and ends with the 32 consecutive
+// columns 32 q .. 32 q + 31 of row n: one MXFP4 block or two NVFP4 blocks,
+// whose scale arithmetic runs once in one lane.  Ranks past r read as zeros,
+// which adds exact zeros.  grid.z is the expert of a stack (expert e0 + z,
+// planes [E, O, *] contiguous, its ws2 in the table).
+// Bound by vector instructions (unpacking A, the bf16 rounding and the codes):
+// 4096 x 4096 at rank 32 took 37.2 us with the rank sum on vector
+// multiply-adds and 8 columns a lane (28 instructions per weight outside the
+// sum, each block's scale in 2 or 4 lanes), 21.3 here; NVFP4 14336 x 4096 at rank 16 95 -> 56.
+constexpr int kReqRows = 64;        // rows per workgroup: 4 waves x 16
+constexpr int kReqCols = 128;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kReqRankTile = 32;    // ranks staged in LDS at a time
-
-// The rank is walked in tiles of 32 (A tile [32][512] and B tile [16][32] in
-// LDS), k in increasing order throughout; ranks past r read as 0, which adds
-// exact zeros.  grid.z is the expert of a stack (expert e0 + z, planes
-// [E, O, *] contiguous, its ws2 in the table).
 template <int FMT>
-__global__ __launch_bounds__(256) void qat_requant_kernel(const uint8_t* __restrict__ codes,
+__global__ __launch_bounds__(256, 4) void qat_requant_kernel(const uint8_t* __restrict__ codes,
                                                           const uint8_t* __restrict__ scales, Ws2Table ws2t,
                                                           const uint16_t* __restrict__ B,
                                                           const uint16_t* __restrict__ A, int O, int I, int r,
-                                                          float c, uint8_t* __restrict__ codes_out,
-                                                          uint8_t* __restrict__ scales_out, int e0) {
+                                                          float c, uint8_t* codes_out, uint8_t* scales_out, int e0) {
   constexpr int BLK = ScaleOperand<FMT>::kBlock;
+  constexpr uint32_t kPast = 0x80000000u;              // an offset past every plane: reads zeros, writes nothing
   {
     const int64_t e = (int64_t)e0 + blockIdx.z;
     const int64_t code_plane = (int64_t)O * (I / 2), scale_plane = (int64_t)O * (I / BLK);
@@ -55,92 +68,124 @@ __global__ __launch_bounds__(256) void qat_requant_kernel(const uint8_t* __restr
     A += e * r * I;
   }
   const float ws2 = FMT == kMX ? 1.0f : ws2t.v[blockIdx.z];
-  __shared__ __align__(16) uint16_t a_lds[kReqRankTile][kReqCols];
-  __shared__ __align__(16) uint16_t b_lds[kReqRows][kReqRankTile];
-  const int tid = threadIdx.x;
-  const int col0 = blockIdx.x * kReqCols, row0 = blockIdx.y * kReqRows;
-  const int wave = tid >> 6, lane = tid & 63;
-  const int cc = (col0 >> 3) + lane;                       // chunk column in the row
-  const bool col_ok = 8 * cc < I;
-  float acc[kReqRowsPerWave][8];
-#pragma unroll
-  for (int j = 0; j < kReqRowsPerWave; ++j)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[j][e] = 0.0f;
-
-  const int rp = (r + 7) & ~7;
-  for (int kb = 0; kb < rp; kb += kReqRankTile) {
-    if (kb > 0) __syncthreads();                           // the previous tile is consumed
-    // A tile: 64 threads per rank row of 512 columns, 16 bytes each.
-    for (int e = tid; e < kReqRankTile * (kReqCols / 8); e += 256) {
-      const int k = e / (kReqCols / 8), q = e % (kReqCols / 8);
-      const int col = col0 + 8 * q;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (kb + k < r && col < I) v = *reinterpret_cast<const uint4*>(A + (int64_t)(kb + k) * I + col);
-      *reinterpret_cast<uint4*>(&a_lds[k][8 * q]) = v;
-    }
-    for (int e = tid; e < kReqRows * kReqRankTile; e += 256) {
-      const int j = e / kReqRankTile, k = e % kReqRankTile;
-      const int o = row0 + j;
-      b_lds[j][k] = (kb + k < r && o < O) ? B[(int64_t)o * r + kb + k] : (uint16_t)0;
+  // NVFP4: fp32(e4m3 ws2) of every scale byte and its reciprocal (rtn_block16_nv)
+  __shared__ float tab[FMT == kNV ? 256 : 1];
+  RcpDivisor wd{};
+  if constexpr (FMT == kNV) {
+    wd = make_rcp_divisor(ws2);
+    if (threadIdx.x < 128) {
+      const float v = __fmul_rn(e4m3_to_f32(threadIdx.x), ws2);
+      tab[2 * threadIdx.x] = v;
+      tab[2 * threadIdx.x + 1] = __fdiv_rn(1.0f, v);
     }
     __syncthreads();
-    const int kn = min(kReqRankTile, rp - kb);
-    for (int kg = 0; kg < kn; kg += 8) {
-      uint4 bq[kReqRowsPerWave];
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15, q = lane >> 4;
+  const int col0 = blockIdx.x * kReqCols, o0 = blockIdx.y * kReqRows + 16 * wave;
+  if (o0 >= O) return;
+  const int o = o0 + n, i0 = col0 + 32 * q;            // this lane's row and its first column
+  const __amdgpu_buffer_rsrc_t rc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(codes), (short)0, (int)((uint32_t)O * (uint32_t)(I / 2)), 0x00020000);
+  const uint32_t cat = o < O && i0 < I ? (uint32_t)o * (uint32_t)(I / 2) + (uint32_t)(i0 / 2) : kPast;
+  u32x4 cw;
+  uint32_t sb[2] = {0, 0};
+  const int64_t sat = (int64_t)o * (I / BLK) + i0 / BLK;
+  if constexpr (FMT == kMX) {
+    cw = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rc, (int)cat, 0, 0));
+    sb[0] = scales[cat != kPast ? sat : 0];
+  } else {
+    // (I is a multiple of 16: the second block may lie past the row)
+    const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rc, (int)cat, 0, 0));
+    const u32x2 hi = __builtin_bit_cast(
+        u32x2, __builtin_amdgcn_raw_buffer_load_b64(rc, (int)(i0 + 16 < I && cat != kPast ? cat + 8u : kPast), 0, 0));
+    cw = u32x4{lo[0], lo[1], hi[0], hi[1]};
+    sb[0] = scales[cat != kPast ? sat : 0];
+    sb[1] = scales[cat != kPast && i0 + 16 < I ? sat + 1 : 0];
+  }
+  f32x4 acc[8];
 #pragma unroll
-      for (int j = 0; j < kReqRowsPerWave; ++j)
-        bq[j] = *reinterpret_cast<const uint4*>(&b_lds[wave * kReqRowsPerWave + j][kg]);
+  for (int u = 0; u < 8; ++u) acc[u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const uint16_t* ap = A + (col0 + 8 * n < I ? col0 + 8 * n : 0);
+  const uint16_t* bp = B + (int64_t)(o < O ? o : 0) * r;
+  for (int k0 = 0; k0 < r; k0 += 16) {
+    uint4 av[4];
+    uint16_t bv[4];
 #pragma unroll
-      for (int kk = 0; kk < 8; ++kk) {
-        const uint4 av = *reinterpret_cast<const uint4*>(&a_lds[kg + kk][8 * lane]);
-        const uint32_t aw[4] = {av.x, av.y, av.z, av.w};
-        float a[8];
+    for (int s = 0; s < 4; ++s) {
+      const int k = k0 + 4 * s + q, kc = k < r ? k : 0;
+      av[s] = *reinterpret_cast<const uint4*>(ap + (int64_t)kc * I);
+      bv[s] = bp[kc];
+    }
+    if (k0 + 16 > r) {                                 // the last ranks: zeros past r
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          a[2 * p] = __uint_as_float(aw[p] << 16);
-          a[2 * p + 1] = __uint_as_float(aw[p] & 0xFFFF0000u);
+      for (int s = 0; s < 4; ++s)
+        if (k0 + 4 * s + q >= r) {
+          av[s] = make_uint4(0, 0, 0, 0);
+          bv[s] = 0;
         }
+    }
 #pragma unroll
-        for (int j = 0; j < kReqRowsPerWave; ++j) {
-          const uint32_t bw[4] = {bq[j].x, bq[j].y, bq[j].z, bq[j].w};
-          const uint32_t h = bw[kk >> 1];
-          const float b = __uint_as_float((kk & 1) ? (h & 0xFFFF0000u) : (h << 16));
+    for (int s = 0; s < 4; ++s) {
+      const float b = __uint_as_float((uint32_t)bv[s] << 16);
+      const uint32_t w[4] = {av[s].x, av[s].y, av[s].z, av[s].w};
 #pragma unroll
-          for (int e = 0; e < 8; ++e) acc[j][e] = __builtin_fmaf(b, a[e], acc[j][e]);   // b*a exact in fp32
-        }
+      for (int u = 0; u < 8; ++u) {
+        const float a = __uint_as_float(u & 1 ? w[u / 2] & 0xFFFF0000u : w[u / 2] << 16);
+        acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc[u], 0, 0, 0);
       }
     }
   }
-
-  const int64_t cpr = I / 8;                               // chunks per row
+  // column i0 + 8 e + u of row o is register e of tile u
+  uint32_t h[16];
 #pragma unroll
-  for (int j = 0; j < kReqRowsPerWave; ++j) {
-    const int o = row0 + wave * kReqRowsPerWave + j;
-    const bool ok = col_ok && o < O;
-    uint32_t cw = 0, sb = 0;
-    if (ok) {
-      cw = *reinterpret_cast<const uint32_t*>(codes + (int64_t)o * (I / 2) + 4 * cc);
-      sb = scales[(int64_t)o * (I / BLK) + (8 * cc) / BLK];
-    }
+  for (int e = 0; e < 4; ++e) {
     float eff;
-    if (FMT == kMX) eff = e8m0_to_f32(sb);
-    else eff = __fmul_rn(e4m3_to_f32(sb), ws2);
-    uint32_t wb[4];
+    if constexpr (FMT == kMX) eff = e8m0_to_f32(sb[0]);
+    else eff = __fmul_rn(e4m3_to_f32(sb[e >> 1]), ws2);
+    auto pair = [&](auto P) {
+      constexpr int p = decltype(P)::value;
+      const f32x2 v = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(cw[e], 1.0f, p);      // exact E2M1 values
+      f32x2 w;
+      w[0] = __fadd_rn(__fmul_rn(v[0], eff), __fmul_rn(c, acc[2 * p][e]));
+      w[1] = __fadd_rn(__fmul_rn(v[1], eff), __fmul_rn(c, acc[2 * p + 1][e]));
+      h[4 * e + p] = bits_of(__builtin_convertvector(w, bf16x2));
+    };
+    pair(std::integral_constant<int, 0>{});
+    pair(std::integral_constant<int, 1>{});
+    pair(std::integral_constant<int, 2>{});
+    pair(std::integral_constant<int, 3>{});
+  }
+  // a NaN weight is the positive quiet NaN, whatever the convert made of it
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  u16x2 top = {0, 0};
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      uint32_t h2[2];
+  for (int k = 0; k < 16; ++k) top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, h[k] & 0x7FFF7FFFu));
+  if (max((uint32_t)top[0], (uint32_t)top[1]) > 0x7F80u) {
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const int e = 2 * p + q;
-        const float base = __fmul_rn(e2m1_to_f32((cw >> (4 * e)) & 15u), eff);
-        const float w = __fadd_rn(base, __fmul_rn(c, acc[j][e]));
-        h2[q] = (w != w) ? 0x7FC0u : f32_to_bf16_rne(w);
-      }
-      wb[p] = h2[0] | (h2[1] << 16);
+    for (int k = 0; k < 16; ++k) {
+      if ((h[k] & 0x7FFFu) > 0x7F80u) h[k] = (h[k] & 0xFFFF0000u) | 0x7FC0u;
+      if ((h[k] & 0x7FFF0000u) > 0x7F800000u) h[k] = (h[k] & 0xFFFFu) | 0x7FC00000u;
     }
-    rtn_chunk<FMT, kRuleEven>(make_uint4(wb[0], wb[1], wb[2], wb[3]), (int64_t)o * cpr + cc, ok, nullptr, ws2,
-                              nullptr, 0, codes_out, scales_out);
+  }
+  if constexpr (FMT == kMX) {
+    uint32_t packed[4];
+    const uint32_t s = rtn_block32_mx(h, packed);
+    const __amdgpu_buffer_rsrc_t ro =
+        __builtin_amdgcn_make_buffer_rsrc(codes_out, (short)0, (int)((uint32_t)O * (uint32_t)(I / 2)), 0x00020000);
+    __builtin_amdgcn_raw_buffer_store_b128(u32x4{packed[0], packed[1], packed[2], packed[3]}, ro, (int)cat, 0, 0);
+    if (cat != kPast) scales_out[sat] = (uint8_t)s;
+  } else {
+    const __attribute__((address_space(3))) float* tl = (const __attribute__((address_space(3))) float*)tab;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const bool ok = cat != kPast && i0 + 16 * b < I;
+      const uint4 lo = make_uint4(h[8 * b], h[8 * b + 1], h[8 * b + 2], h[8 * b + 3]);
+      const uint4 hi = make_uint4(h[8 * b + 4], h[8 * b + 5], h[8 * b + 6], h[8 * b + 7]);
+      if (wd.d >= 0x1p-55f && wd.d <= 0x1p55f)
+        rtn_block16_nv<kRuleEven, 1>(lo, hi, sat + b, ok, wd, tl, codes_out, scales_out, 0);
+      else
+        rtn_block16_nv<kRuleEven, -1>(lo, hi, sat + b, ok, wd, tl, codes_out, scales_out, 0);
+    }
   }
 }
 
@@ -401,7 +446,7 @@ struct TmList {
 static_assert(sizeof(TmList) <= 4096, "kernel argument budget");
 
 template <int JT>
-__global__ __launch_bounds__(256) void thin_m_kernel(TmList pl) {
+__global__ __launch_bounds__(256, 2) void thin_m_kernel(TmList pl) {
   constexpr int RW = 32 * JT;
   constexpr int kAChunks = 2 * RW * (kTmTok / 8) / 256;   // 16-byte A chunks per thread per stage
   __shared__ __align__(16) uint16_t rt[kTmTok * kTmCols];

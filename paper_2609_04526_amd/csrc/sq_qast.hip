@@ -85,7 +85,7 @@ __device__ __forceinline__ void base4(uint32_t (&in)[4], const uint8_t* base, si
 // o.  4096 x 256 scales at rank 58: 12.2 us on vector multiply-adds fed from
 // LDS, 9.4 here; 4096 x 128 at rank 32 6.6 -> 5.8.
 template <int FMT, int RMAX, int GB>
-__global__ __launch_bounds__(256) void qast_scales_kernel(const uint8_t* __restrict__ base,
+__global__ __launch_bounds__(256, 4) void qast_scales_kernel(const uint8_t* __restrict__ base,
                                                           const uint16_t* __restrict__ B,
                                                           const uint16_t* __restrict__ A, int O, int G, int r,
                                                           float c, Ws2Table ws2, uint8_t* out, uint8_t* mask,
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(256) void qast_scales_kernel(const uint8_t* __restr
 // (NVFP4): 82 us on vector multiply-adds fed from LDS, 57 with A loaded by
 // every wave, 50 now.
 template <int FMT, int RMAX, int GB, int W>
-__global__ __launch_bounds__(256) void qast_scales_wide_kernel(const uint8_t* __restrict__ base,
+__global__ __launch_bounds__(256, 4) void qast_scales_wide_kernel(const uint8_t* __restrict__ base,
                                                                const uint16_t* __restrict__ B,
                                                                const uint16_t* __restrict__ A, int O, int G, int r,
                                                                float c, Ws2Table ws2, uint8_t* out, uint8_t* mask,
@@ -225,11 +225,15 @@ __global__ __launch_bounds__(256) void qast_scales_wide_kernel(const uint8_t* __
 // order.  Column n of tile u is block U n + u, so that a lane's blocks are one
 // load of dS, and row n of tile t is rank RT n + t.  U = 4, but 2 for ranks over
 // 32: with 16 accumulator tiles a wave, too few waves fit a SIMD (128 experts
-// of 768 x 128 at rank 54: 113 us, 76 with 8).  Chunks are added in order by
+// of 768 x 128 at rank 54: 113 us, 69 with 8).  Chunks are added in order by
 // qast_da_reduce_kernel.
 // 4096 x 256 scales at rank 58: vector multiply-adds fed from LDS tiles took
 // 30.0 us, this 11.2; the reduction of 128 partial planes of 32 rows (a wave
 // per output, lanes striding over the planes) 12.3, of 64 in rows 3.9.
+// The launch bounds of the MFMA kernels here ask for four waves per SIMD: left
+// free, the compiler kept the accumulators in accumulation registers and
+// moved every operand through them (128 experts of 2048 x 24 at rank 32: the
+// gradients 45 -> 36 us).
 constexpr int kDaRows = 64;         // rows per dA chunk
 template <int RT>
 __host__ __device__ constexpr int da_u() { return RT == 4 ? 2 : 4; }
@@ -410,7 +414,7 @@ __device__ __forceinline__ void da_tile(int bx, int e, float* lds, const float* 
 }
 
 template <int RT>
-__global__ __launch_bounds__(256) void qast_grads_kernel(const float* __restrict__ dS,
+__global__ __launch_bounds__(256, 4) void qast_grads_kernel(const float* __restrict__ dS,
                                                          const uint8_t* __restrict__ mask,
                                                          const uint16_t* __restrict__ A,
                                                          const uint16_t* __restrict__ B, int O, int G, int r,

@@ -428,4 +428,56 @@ __device__ __forceinline__ void rtn_block16_nv(const uint4 lo, const uint4 hi, i
   }
 }
 
+// MXFP4 nearest-even re-quantisation of one whole 32-weight block per lane
+// (16 words of bf16 pairs): the arithmetic of rtn_chunk<kMX, kRuleEven> with
+// the scale taken once per block.  Returns the scale byte.
+__device__ __forceinline__ uint32_t rtn_block32_mx(const uint32_t (&h)[16], uint32_t (&packed)[4]) {
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  u16x2 m2 = {0, 0};
+#pragma unroll
+  for (int k = 0; k < 16; ++k) m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(u16x2, h[k] & 0x7FFF7FFFu));
+  const uint32_t am = max((uint32_t)m2[0], (uint32_t)m2[1]);
+  const float amax = __uint_as_float(am << 16);
+  const float sixth = amax >= 0x1p-120f ? div_exact<1>(amax, RcpDivisor{6.0f, 0x1.555556p-3f, true})
+                                        : __fdiv_rn(amax, 6.0f);
+  uint32_t sbyte;
+  float inv;                                        // 2^-k; NaN for a NaN block
+  if (sixth != sixth) {
+    sbyte = 0xFFu;
+    inv = __uint_as_float(0x7FC00000u);
+  } else {
+    int k;
+    if (sixth == 0.0f) k = -127;
+    else if (sixth > 3.4028234e38f) k = 127;
+    else k = ceil_log2_pos(sixth);
+    k = k < -127 ? -127 : (k > 127 ? 127 : k);
+    sbyte = (uint32_t)(k + 127);
+    inv = (k == 127) ? __uint_as_float(0x00400000u) : __uint_as_float((uint32_t)(127 - k) << 23);
+  }
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    float q[8];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      q[2 * k] = __fmul_rn(__uint_as_float(h[4 * w + k] << 16), inv);
+      q[2 * k + 1] = __fmul_rn(__uint_as_float(h[4 * w + k] & 0xFFFF0000u), inv);
+    }
+    uint32_t c = 0;
+    c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(c, q[0], q[1], 1.0f, 0);
+    c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(c, q[2], q[3], 1.0f, 1);
+    c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(c, q[4], q[5], 1.0f, 2);
+    c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(c, q[6], q[7], 1.0f, 3);
+    if (am > 0x7F80u) {                             // a NaN in the block: the sign of w, magnitude 0 for NaN
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const uint32_t hb = (h[4 * w + (k >> 1)] >> (16 * (k & 1))) & 0xFFFFu;
+        const uint32_t mag = (q[k] != q[k]) ? 0u : ((c >> (4 * k)) & 7u);
+        c = (c & ~(15u << (4 * k))) | ((mag | ((hb >> 12) & 8u)) << (4 * k));
+      }
+    }
+    packed[w] = c;
+  }
+  return sbyte;
+}
+
 }  // namespace sq
