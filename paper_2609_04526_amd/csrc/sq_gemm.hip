@@ -459,13 +459,8 @@ __device__ __forceinline__ void ds_store(const f32x16 (&acc)[TM][TN], const u32x
 // product, dealt to XCDs by bid % 8; with ORDERED, bid is already the tile's
 // position in the product's tile order (the grouped launch deals its XCD
 // stretches over all experts at once).
-// With THIN the workgroup may instead take a strip of an expert with few
-// tokens (thin_strip): a grouped call whose experts are mostly larger runs its
-// few small ones in the same launch.
-constexpr int kFuseNt = 2;                     // a fused strip: 16 tokens x 32 columns
-template <int MODE, int FMT, int BM, int BN, int WGM, int WGN, int STAGES, int BK, bool ORDERED = false,
-          bool THIN = false>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bid, int nb, bool thin_strip = false) {
+template <int MODE, int FMT, int BM, int BN, int WGM, int WGN, int STAGES, int BK, bool ORDERED = false>
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bid, int nb) {
   constexpr int NT = 64 * WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int TM = WM / 32, TN = WN / 32;
@@ -512,29 +507,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bid, int nb, bo
   else tile_of<group_m<MODE>()>((MODE == kDs && g.ksplit > 1) ? bid - split * tiles : bid, (MODE == kDs && g.ksplit > 1) ? tiles : nb,
                                 tiles_m, tiles_n, tm, tn);
   const int m0 = g.m_off + tm * BM, n0 = g.n_off + tn * BN;
-
-  if constexpr (THIN) {
-    if (thin_strip) {
-      constexpr int kWave = MODE == kDx ? thin_dx_wave_bytes<1, 1>() : thin_fwd_wave_bytes<1, kFuseNt, 1>();
-      constexpr int kPer = L::kStageAlloc / kWave, kPerW = (kWReg ? L::kWBytes : 0) / kWave;
-      static_assert(NT == kThinThreads && STAGES != 3 && STAGES * kPer + kPerW >= kThinKWaves, "a region per wave");
-      auto region = [&](int w) -> SQ_LDS uint8_t* {
-        if (w < kPerW) return (SQ_LDS uint8_t*)ldsw + w * kWave;
-        w -= kPerW;
-        if (w < kPer) return (SQ_LDS uint8_t*)lds0 + w * kWave;
-        if constexpr (STAGES > 2) {
-          if (w >= 2 * kPer)
-            return w < 3 * kPer ? (SQ_LDS uint8_t*)lds2 + (w - 2 * kPer) * kWave
-                                : (SQ_LDS uint8_t*)lds3 + (w - 3 * kPer) * kWave;
-        }
-        return (SQ_LDS uint8_t*)lds1 + (w - kPer) * kWave;
-      };
-      const int tiles_t = (g.T + 15) / 16;
-      if constexpr (MODE == kDx) thin_dx_tile<FMT, 1, 1>(g, bid % tiles_t, bid / tiles_t, region);
-      else thin_fwd_tile<FMT, 1, kFuseNt, 1>(g, bid % tiles_t, bid / tiles_t, region);
-      return;
-    }
-  }
 
   auto stage = [&](auto SC) -> SQ_LDS uint8_t* {
     constexpr int S = decltype(SC)::value;
@@ -1083,7 +1055,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(GemmArgs g) {
 // L2 and read its activation and weight panels from HBM about once; dealing
 // every expert's tiles over all 8 XCDs made each L2 fetch them again (the
 // 128-expert MoE layer moved 4 to 8 times its operand bytes).
-template <int MODE, int FMT, bool THIN, int BM, int BN, int WGM, int WGN, int STAGES, int BK>
+template <int MODE, int FMT, int BM, int BN, int WGM, int WGN, int STAGES, int BK>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_grouped_kernel(GemmGroup gg) {
   const int b = xcd_stretch((int)blockIdx.x, (int)gridDim.x);
   int lo = 0, hi = gg.count - 1;                 // last e with tile_begin[e] <= b
@@ -1103,12 +1075,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_grouped_kernel(GemmGroup 
   g.ws2 = gg.ws2[e];
   if (MODE == kDs) g.K = g.T;
   else g.M = g.T;
-  const bool strip = THIN && thin_takes(g.T, g.K);
-  const int tiles = strip ? ((g.T + 15) / 16) * ((g.N + 16 * kFuseNt - 1) / (16 * kFuseNt))
-                          : ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
+  const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   const int local = b - gg.tile_begin[e];
   if (local >= tiles) return;
-  gemm_tile<MODE, FMT, BM, BN, WGM, WGN, STAGES, BK, true, THIN>(g, local, tiles, strip);
+  gemm_tile<MODE, FMT, BM, BN, WGM, WGN, STAGES, BK, true>(g, local, tiles);
 }
 
 // Streamed grouped dS.  With a few hundred tokens per expert a dS tile holds
@@ -1367,6 +1337,33 @@ static int launch_gemm(const GemmArgs& g, hipStream_t s) {
 #define SQ_CFG_HALF_N_DS 256, 128, 4, 2, 3, 64
 #define SQ_CFG_HALF_M_DS 128, 256, 2, 4, 3, 64
 
+// Single products whose grid leaves the chip idle take narrower tiles (the
+// per-element sums are the same in every configuration, so results do not
+// depend on the choice); a stage's round trip, not its work, sets the pace
+// there, and more and smaller workgroups per CU overlap more of them.  By the
+// number n of 128 x 128 tiles, measured at K = 4096 and 14336, us:
+//   MXFP4 forward  n <= 192: 64 x 64, 4 waves, four stages (40 KiB: four per
+//                  CU): n = 32 38.0 -> 25.1, 128 40.6 -> 29.2, 192 42.1 -> 36.7;
+//                  n <= 352: 64 x 128, 4 waves: n = 224 42.8 -> 38.0, 352 57.3
+//                  -> 54.3 (448: 59.3 either way)
+//   NVFP4 forward  n <= 256: 128 x 64: n = 64 46.4 -> 34.0, 128 46.1 -> 34.3,
+//                  256 49.9 -> 48.9
+//   dX             n <= 128: 64 x 128: n = 32 43.3 -> 36.1, 128 42.9 -> 38.2
+//                  (192: 45.0 -> 49.2)
+// Above those, the NVFP4 forward and dX over at least 2048 terms take 256 x 128
+// tiles where they fill their rounds (one round at least 0.7 full, or two
+// 0.85): 4096 x 4096 at 1999 tokens (256 of them) 79.7 -> 73.4 and 72.2 -> 63.6,
+// 1400 tokens (192) 69.5 -> 66.8 and 64.7 -> 58.2, but 3000 tokens (384) 120 ->
+// 133 and 106 -> 117; dX over 1024 terms 23.4 -> 25.0.
+#define SQ_CFG_FEW_FWDC 64, 64, 2, 2, 4, 64
+#define SQ_CFG_MID_FWDC 64, 128, 1, 4, 4, 64
+#define SQ_CFG_FEW_FWDR 128, 64, 4, 2, 2, 64
+#define SQ_CFG_FEW_DX 64, 128, 2, 4, 2, 64
+// A second round of 256 x 256 tiles less than 0.4 full that cannot be cut off
+// (below) costs more than 128 x 128 tiles throughout: 14336 x 4096 at 1400
+// tokens (336 tiles) 178 -> 155 us MXFP4, 225 -> 190 NVFP4, 4096 x 14336 dX 189
+// -> 170.
+
 // A grid of 256 x 256 tiles that ends in a partial wave (at most half the
 // CUs busy) leaves the other CUs idle while it runs.  When that last partial
 // wave is whole tile-columns (or tile-rows) of the output, those columns
@@ -1381,6 +1378,22 @@ template <int MODE, int FMT, int BM, int BN, int... REST>
 static int launch_sized(const GemmArgs& g, hipStream_t s) {
   const int tm = (g.M + BM - 1) / BM, tn = (g.N + BN - 1) / BN;
   const int64_t big = (int64_t)tm * tn;
+  if (MODE != kDs && BM == 256 && BN == 256) {
+    const int64_t n = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128);
+    if constexpr (MODE == kFwdC) {
+      if (n <= 192) return launch_gemm<MODE, FMT, SQ_CFG_FEW_FWDC>(g, s);
+      if (n <= 352) return launch_gemm<MODE, FMT, SQ_CFG_MID_FWDC>(g, s);
+    } else if constexpr (MODE == kFwdR) {
+      if (n <= 256) return launch_gemm<MODE, FMT, SQ_CFG_FEW_FWDR>(g, s);
+    } else if constexpr (MODE == kDx) {
+      if (n <= 128) return launch_gemm<MODE, FMT, SQ_CFG_FEW_DX>(g, s);
+    }
+    if constexpr (MODE == kFwdR || MODE == kDx) {
+      const int64_t half = (int64_t)tm * ((g.N + 127) / 128), rounds = (half + kCUs - 1) / kCUs;
+      if (big < kCUs && n > 256 && g.K >= 2048 && half * 100 >= (rounds == 1 ? 70 : 85) * rounds * kCUs)
+        return launch_gemm<MODE, FMT, SQ_CFG_HALF_N>(g, s);
+    }
+  }
   if (big < kCUs) {
     if constexpr (MODE == kFwdC) return launch_gemm<MODE, FMT, SQ_CFG_SMALL_FWDC>(g, s);
     else return launch_gemm<MODE, FMT, SQ_CFG_SMALL>(g, s);
@@ -1409,6 +1422,12 @@ static int launch_sized(const GemmArgs& g, hipStream_t s) {
       if (rc != 0) return rc;
       if constexpr (MODE == kDs) return launch_gemm<MODE, FMT, SQ_CFG_HALF_M_DS>(b, s);
       else return launch_gemm<MODE, FMT, SQ_CFG_HALF_M>(b, s);
+    }
+  }
+  if constexpr (MODE != kDs) {
+    if (big > kCUs && big * 10 < 14 * kCUs) {
+      if constexpr (MODE == kFwdC) return launch_gemm<MODE, FMT, SQ_CFG_SMALL_FWDC>(g, s);
+      else return launch_gemm<MODE, FMT, SQ_CFG_SMALL>(g, s);
     }
   }
   return launch_gemm<MODE, FMT, BM, BN, REST...>(g, s);
@@ -1522,11 +1541,7 @@ int gemm_dx(int fmt, int T, int O, int I, const void* dY, const uint8_t* codes,
 
 // ------------------------------------------------------------------ grouped
 // One launch per kGroupMax experts, one workgroup per tile.
-// THIN: experts that take the few-token kernels (thin_takes) run as strips of
-// 16 tokens x 32 columns in the same launch, so the odd one among larger
-// experts costs no launch of its own.
-static_assert(kThinDxCols == 16 * kFuseNt, "one strip width");
-template <int MODE, int FMT, bool THIN, int BM, int BN, int WGM, int WGN, int STAGES, int BK>
+template <int MODE, int FMT, int BM, int BN, int WGM, int WGN, int STAGES, int BK>
 static int launch_grouped(GemmGroup& gg, const ExpertProblem* p, int n, hipStream_t s) {
   using L = SmemLayout<MODE, BM, BN, STAGES, BK, WGM * WGN>;
   static_assert(L::kBytes <= 160 * 1024, "LDS budget");
@@ -1534,16 +1549,14 @@ static int launch_grouped(GemmGroup& gg, const ExpertProblem* p, int n, hipStrea
   gg.count = n;
   for (int e = 0; e < n; ++e) {
     const int M = MODE == kDs ? gg.base.M : p[e].T;
-    const int tiles = THIN && thin_takes(p[e].T, gg.base.K)
-                          ? ((M + 15) / 16) * ((gg.base.N + 16 * kFuseNt - 1) / (16 * kFuseNt))
-                          : ((M + BM - 1) / BM) * ((gg.base.N + BN - 1) / BN);
+    const int tiles = ((M + BM - 1) / BM) * ((gg.base.N + BN - 1) / BN);
     gg.T[e] = p[e].T;
     gg.ws2[e] = FMT == kNV ? p[e].ws2 : 1.0f;
     gg.tile_begin[e] = blocks;
     blocks += tiles;
   }
   if (blocks == 0) return 0;
-  hipLaunchKernelGGL((gemm_grouped_kernel<MODE, FMT, THIN, BM, BN, WGM, WGN, STAGES, BK>), dim3(blocks),
+  hipLaunchKernelGGL((gemm_grouped_kernel<MODE, FMT, BM, BN, WGM, WGN, STAGES, BK>), dim3(blocks),
                      dim3(64 * WGM * WGN), 0, s, gg);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -1596,12 +1609,11 @@ static int launch_ds_stream(GemmGroup& gg, const ExpertProblem* p, int n, hipStr
 // 1920 tiles to 1536 and 192: 175 -> 180 us, so it stays whole).  If the
 // moved pointers do not fit the launch's 32-bit offsets, the experts run
 // unsplit.
-template <int FMT, bool THIN>
+template <int FMT>
 static int dx_split_tails(GemmGroup& gg, const ExpertProblem* p, int n, hipStream_t s) {
   const int64_t cols = (gg.base.I + 127) / 128, cols_thin = (gg.base.I + 255) / 256;
   int64_t all = 0, kept = 0, moved = 0;
   for (int e = 0; e < n; ++e) {
-    if (THIN && thin_takes(p[e].T, gg.base.O)) continue;          // its own strips, in the first launch
     const int t = p[e].T % 128;
     all += (int64_t)((p[e].T + 127) / 128) * cols;
     if (t > 0 && t <= 64) {
@@ -1613,13 +1625,13 @@ static int dx_split_tails(GemmGroup& gg, const ExpertProblem* p, int n, hipStrea
   }
   const double slots = 2.0 * kCUs;
   if (moved == 0 || (double)kept / slots + 1.15 * (double)((moved + 2 * kCUs - 1) / (2 * kCUs)) >= (double)all / slots)
-    return launch_grouped<kDx, FMT, THIN, SQ_CFG_SMALL>(gg, p, n, s);
+    return launch_grouped<kDx, FMT, SQ_CFG_SMALL>(gg, p, n, s);
   ExpertProblem whole[kGroupMax], tail[kGroupMax];
   int nw = 0, nt = 0;
   const size_t a_row = (size_t)gg.base.O * 2, out_row = (size_t)gg.base.I * (gg.base.out_bf16 ? 2 : 4);
   for (int e = 0; e < n; ++e) {
     const int t = p[e].T % 128;
-    if (t == 0 || t > 64 || (THIN && thin_takes(p[e].T, gg.base.O))) {
+    if (t == 0 || t > 64) {
       whole[nw++] = p[e];
       continue;
     }
@@ -1635,21 +1647,10 @@ static int dx_split_tails(GemmGroup& gg, const ExpertProblem* p, int n, hipStrea
   }
   GemmGroup gw = gg, gt = gg;
   if (nt == 0 || !set_experts(gw, whole, nw, false) || !set_experts(gt, tail, nt, false))
-    return launch_grouped<kDx, FMT, THIN, SQ_CFG_SMALL>(gg, p, n, s);
-  const int rc = nw > 0 ? launch_grouped<kDx, FMT, THIN, SQ_CFG_SMALL>(gw, whole, nw, s) : 0;
+    return launch_grouped<kDx, FMT, SQ_CFG_SMALL>(gg, p, n, s);
+  const int rc = nw > 0 ? launch_grouped<kDx, FMT, SQ_CFG_SMALL>(gw, whole, nw, s) : 0;
   if (rc != 0) return rc;
-  return launch_grouped<kDx, FMT, false, SQ_CFG_GROUPED_THIN>(gt, tail, nt, s);
-}
-
-// Experts that take the few-token kernels run in those when the set holds no
-// others, and share the launch of the small tiles otherwise.
-template <int MODE, int FMT, bool THIN>
-static int grouped_small(GemmGroup& gg, const ExpertProblem* p, int n, int64_t tokens, int64_t others, hipStream_t s) {
-  if constexpr (MODE == kFwdC) return launch_grouped<MODE, FMT, THIN, SQ_CFG_GROUPED_FWDC>(gg, p, n, s);
-  else if constexpr (MODE == kDx) {
-    if (tokens <= 96 * others) return launch_grouped<MODE, FMT, THIN, SQ_CFG_GROUPED_THIN>(gg, p, n, s);
-    return dx_split_tails<FMT, THIN>(gg, p, n, s);
-  } else return launch_grouped<MODE, FMT, THIN, SQ_CFG_SMALL>(gg, p, n, s);
+  return launch_grouped<kDx, FMT, SQ_CFG_GROUPED_THIN>(gt, tail, nt, s);
 }
 
 template <int MODE, int FMT>
@@ -1667,50 +1668,45 @@ static int grouped_thin(GemmGroup& gg, const ExpertProblem* p, int n, hipStream_
 // at least 512 tokens (rows of the forward and dX, the contraction of dS:
 // shorter token sums leave a 256 x 256 dS tile a few stages between its
 // prologue and epilogue, where two 128 x 128 workgroups per CU do better).
+// Experts that take the few-token kernels (as their single calls do) run in a
+// launch of their own.
 template <int MODE, int FMT, int BM, int BN, int... REST>
 static int grouped_sized(GemmGroup& gg, const ExpertProblem* p, int n, hipStream_t s) {
-  int64_t tokens = 0, big = 0;
-  int thin = 0;
-  for (int e = 0; e < n; ++e) {
-    if (MODE != kDs && thin_takes(p[e].T, gg.base.K)) {
-      ++thin;
-      continue;
-    }
-    tokens += p[e].T;
-    const int M = MODE == kDs ? gg.base.M : p[e].T;
-    big += (int64_t)((M + BM - 1) / BM) * ((gg.base.N + BN - 1) / BN);
-  }
-  const int64_t others = n - thin;
-  const bool large = big >= kCUs && tokens >= 512 * others;
-  if constexpr (MODE == kDs) {
-    if (large) return launch_grouped<MODE, FMT, false, BM, BN, REST...>(gg, p, n, s);
-    return launch_ds_stream<FMT, SQ_CFG_DS_STREAM>(gg, p, n, s);
-  } else {
-    if (others == 0) return grouped_thin<MODE, FMT>(gg, p, n, s);
-    const bool longs = MODE == kFwdC && tokens >= 2048 * others;
-    if (!large && !longs)
-      return thin ? grouped_small<MODE, FMT, true>(gg, p, n, tokens, others, s)
-                  : grouped_small<MODE, FMT, false>(gg, p, n, tokens, others, s);
-    // large tiles for the others, a launch of their own for the few-token ones
-    ExpertProblem sub[kGroupMax];
-    if (thin) {
-      int m = 0;
-      for (int e = 0; e < n; ++e)
-        if (thin_takes(p[e].T, gg.base.K)) sub[m++] = p[e];
-      if (!set_experts(gg, sub, m, false)) return -1;     // a part of a set that fits
-      const int rc = grouped_thin<MODE, FMT>(gg, sub, m, s);
+  ExpertProblem sub[kGroupMax];
+  if constexpr (MODE != kDs) {
+    int few = 0;
+    for (int e = 0; e < n; ++e)
+      if (thin_takes(p[e].T, gg.base.K)) sub[few++] = p[e];
+    if (few == n) return grouped_thin<MODE, FMT>(gg, p, n, s);
+    if (few > 0) {
+      if (!set_experts(gg, sub, few, false)) return -1;       // a part of a set that fits
+      const int rc = grouped_thin<MODE, FMT>(gg, sub, few, s);
       if (rc != 0) return rc;
-      m = 0;
+      int m = 0;
       for (int e = 0; e < n; ++e)
         if (!thin_takes(p[e].T, gg.base.K)) sub[m++] = p[e];
       if (!set_experts(gg, sub, m, false)) return -1;
       p = sub;
       n = m;
     }
-    if (large) return launch_grouped<MODE, FMT, false, BM, BN, REST...>(gg, p, n, s);
-    if constexpr (MODE == kFwdC) return launch_grouped<MODE, FMT, false, SQ_CFG_GROUPED_FWDC_LONG>(gg, p, n, s);
-    return -1;                                            // not reached: `longs` is the register forward's
   }
+  int64_t tokens = 0, big = 0;
+  for (int e = 0; e < n; ++e) {
+    tokens += p[e].T;
+    const int M = MODE == kDs ? gg.base.M : p[e].T;
+    big += (int64_t)((M + BM - 1) / BM) * ((gg.base.N + BN - 1) / BN);
+  }
+  const bool large = big >= kCUs && tokens >= (int64_t)512 * n;
+  if (large) return launch_grouped<MODE, FMT, BM, BN, REST...>(gg, p, n, s);
+  if constexpr (MODE == kFwdC) {
+    if (tokens >= (int64_t)2048 * n) return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_FWDC_LONG>(gg, p, n, s);
+    return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_FWDC>(gg, p, n, s);
+  }
+  else if constexpr (MODE == kDs) return launch_ds_stream<FMT, SQ_CFG_DS_STREAM>(gg, p, n, s);
+  else if constexpr (MODE == kDx) {
+    if (tokens <= (int64_t)96 * n) return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_THIN>(gg, p, n, s);
+    return dx_split_tails<FMT>(gg, p, n, s);
+  } else return launch_grouped<MODE, FMT, SQ_CFG_SMALL>(gg, p, n, s);
 }
 
 template <int MODE>

@@ -36,12 +36,13 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // length K (I in the forward, O in dX).  Single products are faster here up to
 // 64 tokens at every size tried (see thin_fwd_pick).  But a strip is a third
 // as efficient as a tile once experts fill the chip, and an expert has to
-// take the path its single call takes: with 64 tokens for every K, the routed
-// split of the 128-expert MoE layer (K = 768 and 2048, a tenth of the experts
-// under 65 rows) went from 512 to 528 us with its small experts in a launch
-// of their own and to 561 us with them among the tiles.  So contractions as
-// short as those stop at 16 tokens, where strip and tile cost the same.
-__host__ __device__ inline bool thin_takes(int T, int K) { return T <= (K > 2048 ? 64 : 16); }
+// take the path its single call takes.  So contractions as short as the
+// 30B-A3B MoE's (768 and 2048) stay on tiles: with 64 tokens for every K its
+// layer at 4096 tokens (a tenth of the experts under 65 rows) went from 512 to
+// 528 us with the small experts in a launch of their own and to 561 with them
+// among the tiles, and with 16 tokens its layer at 326 tokens from 154 to 185
+// (single products of that length are near the launch's own time either way).
+__host__ __device__ inline bool thin_takes(int T, int K) { return K > 2048 && T <= 64; }
 
 constexpr int kThinKWaves = 8;             // waves that split the contraction
 constexpr int kThinThreads = 64 * kThinKWaves;

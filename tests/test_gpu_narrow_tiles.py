@@ -1,0 +1,52 @@
+"""Parity of the tiles that single products take when their grid leaves the
+chip idle: 64 x 64 and 64 x 128 (MXFP4 forward), 128 x 64 (NVFP4 forward), 64 x
+128 (dX), 256 x 128 (NVFP4 forward and dX) and 128 x 128 after a thin second
+round of large tiles.  Ragged in every dimension, on both sides of each limit,
+against the oracle per element; a grouped call of the same expert, whose tiles
+differ, gives the same bits."""
+
+import pytest
+import torch
+
+from conftest import ensure_library, gpu_ready
+from test_gpu_gemm import make_layer, to_dev
+from test_gpu_thin import check
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not gpu_ready(), reason="needs a GPU")]
+
+
+@pytest.fixture(scope="module")
+def sq():
+    ensure_library()
+    from paper_2609_04526_amd import sq as _sq
+    return _sq
+
+
+def tiles(M, N):
+    return -(-M // 128) * -(-N // 128)
+
+
+SHAPES = [
+    ("mx", 65, 72, 256), ("nv", 65, 72, 272),              # one tile, one row over 64
+    ("mx", 193, 200, 1024), ("nv", 193, 200, 528),
+    ("mx", 1500, 2040, 256), ("mx", 1540, 2056, 256),       # 192 and 221 tiles: 64 x 64, 64 x 128
+    ("mx", 2800, 2040, 256), ("mx", 2820, 2056, 256),       # 352 and 391: 64 x 128, 128 x 128
+    ("nv", 2030, 2040, 272), ("nv", 2050, 2056, 272),       # 256 and 289 tiles
+    ("mx", 1000, 264, 2040 // 32 * 32), ("nv", 1030, 264, 2032),   # dX: 128 tiles and more
+    ("nv", 2040, 4104, 2064), ("mx", 1290, 2056, 4128),     # 256 x 128 tiles over long sums
+    ("mx", 1290, 14344, 64), ("nv", 1290, 14344, 64),       # 342 large tiles: a thin second round
+]
+
+
+@pytest.mark.parametrize("fmt,T,O,I", SHAPES)
+def test_parity_and_grouped_bits(sq, fmt, T, O, I):
+    X, dY, codes, sb, ws2 = make_layer(fmt, T, O, I, seed=9700 + T + O)
+    Xc, dYc, c, s = to_dev(X, dY, codes, sb)
+    print(f"[narrow] fmt={fmt} T={T} O={O} I={I} tiles fwd {tiles(T, O)} dx {tiles(T, I)}", flush=True)
+    Y, dX = sq.sq_fwd(fmt, Xc, c, s, ws2), sq.sq_bwd_dx(fmt, dYc, c, s, ws2)
+    Yb, dXb = (sq.sq_fwd(fmt, Xc, c, s, ws2, torch.bfloat16), sq.sq_bwd_dx(fmt, dYc, c, s, ws2, torch.bfloat16))
+    check(fmt, X, dY, codes, sb, ws2, Y.cpu().numpy(), dX.cpu().numpy(), f"{fmt} {T}x{O}x{I}")
+    assert torch.equal(Yb, Y.to(torch.bfloat16)) and torch.equal(dXb, dX.to(torch.bfloat16))
+    Yg = sq.sq_fwd_grouped(fmt, [Xc, Xc[:70]], [c, c], [s, s], [ws2, ws2])
+    dXg = sq.sq_bwd_dx_grouped(fmt, [dYc, dYc[:70]], [c, c], [s, s], [ws2, ws2])
+    assert torch.equal(Yg[0], Y) and torch.equal(dXg[0], dX)

@@ -1,6 +1,5 @@
 """GPU parity of the few-token forward and dX (csrc/sq_thin.h): calls and
-experts of up to 64 tokens over contractions longer than 2048, of up to 16
-tokens over shorter ones.  Sizes sit at the edges of the 16-token tiles, of
+experts of up to 64 tokens over contractions longer than 2048.  Sizes sit at the edges of the 16-token tiles, of
 the 16-, 32- and 64-column strips and of the 128-deep (forward) and 64-deep
 (dX) steps that the 8 waves share; every element is held to the summation
 bound of tests/parity_check.py against the oracle, and every expert of a
@@ -27,7 +26,7 @@ def sq():
 
 
 def takes(T, K):
-    return T <= (64 if K > 2048 else 16)
+    return K > 2048 and T <= 64
 
 
 def check(fmt, X, dY, codes, sb, ws2, Y, dX, what):
@@ -42,8 +41,8 @@ def check(fmt, X, dY, codes, sb, ws2, Y, dX, what):
 
 
 @pytest.mark.parametrize("fmt,T,O,I", [
-    ("mx", 1, 8, 32), ("nv", 1, 8, 16),                 # smallest layer
-    ("mx", 16, 40, 160), ("nv", 15, 72, 144),            # a token tile and one row less, ragged strips and steps
+    ("mx", 1, 8, 2080), ("nv", 1, 2056, 16),             # the narrowest strips, one token
+    ("mx", 16, 40, 2208), ("nv", 15, 2072, 144),         # a token tile and one row less, ragged strips and steps
     ("mx", 17, 2056, 2080), ("nv", 17, 2056, 2064),      # long contractions both ways, one row over a tile
     ("mx", 33, 2064, 2176), ("nv", 33, 4104, 2096),
     ("mx", 64, 2056, 4128), ("nv", 64, 2072, 4112),      # the most tokens; NVFP4 rows ending inside a 32-code chunk
@@ -72,8 +71,8 @@ def test_parity(sq, fmt, T, O, I):
 @pytest.mark.parametrize("fmt", ["mx", "nv"])
 @pytest.mark.parametrize("Ts,O,I", [
     ([1, 16, 17, 64, 33, 5], 2056, 2112),                # only few-token experts, mixed tiles
-    ([3, 16, 0, 7], 96, 160),
-    ([1, 16, 17, 65, 64, 200, 9], 2056, 2304),           # among larger experts: strips in the tiles' launch
+    ([3, 16, 0, 7], 96, 2208),
+    ([1, 16, 17, 65, 64, 200, 9], 2056, 2304),           # among larger experts: a launch of their own
     ([16, 17, 300, 1, 129], 264, 512),
     ([2200, 12, 2100], 2056, 2304),                      # beside experts on the long or large tiles
 ])
