@@ -1590,6 +1590,18 @@ static int launch_ds_stream(GemmGroup& gg, const ExpertProblem* p, int n, hipStr
 // (at 64 tokens 184 -> 117 us; at 256, 72 -> 82 us, where 128 x 128 wins).
 #define SQ_CFG_GROUPED_FWDC 64, 256, 1, 8, 4, 64
 #define SQ_CFG_GROUPED_THIN 64, 256, 1, 8, 2, 64
+// Experts of a few tokens each (a serving batch over an MoE layer) are bound by
+// the weights' round trips and their padding: 32 x 128 tiles, 4 waves, so that
+// four to six workgroups share a CU.  128 experts of 768 x 2048, us, at 1, 4
+// and 12 tokens on average: MXFP4 forward 23.5, 32.8, 33.8 -> 17.4, 23.4, 30.4
+// (31 tokens: 36.6 -> 37.9); dX 28.6, 36.3, 35.7 -> 21.5, 28.3, 33.2 (44.5 ->
+// 41.5, but 2048 x 768 42.8 -> 47.4): up to 16 tokens.  NVFP4 forward 38.9, 55.5
+// -> 26.0, 34.8, and from 12 tokens on 64 x 128 is the faster: 58.0 -> 41.3, 31
+// tokens 60.6 -> 55.7, 62 tokens 74.3 -> 66.9 (125: 99 -> 105): 32 x 128 up to 8,
+// 64 x 128 up to 96.
+#define SQ_CFG_GROUPED_FEW_FWDC 32, 128, 1, 4, 4, 64
+#define SQ_CFG_GROUPED_FEW 32, 128, 1, 4, 2, 64
+#define SQ_CFG_GROUPED_MID_FWDR 64, 128, 2, 4, 2, 64
 // Experts of at least 2048 tokens whose 256 x 256 tiles would not fill the
 // chip (the 8B step's k and v projections, 1024 x 4096 at 4096 tokens, as
 // one grouped forward) take 128 x 256 tiles, 8 waves of 64 x 64, four stages:
@@ -1664,6 +1676,23 @@ static int grouped_thin(GemmGroup& gg, const ExpertProblem* p, int n, hipStream_
   else return thin_fwd<FMT>(nullptr, &gg, s);
 }
 
+// Grouped dX over many tiles takes 64 x 256 throughout where its finer token
+// tiles leave a tenth of the work out: 128 experts of 768 x 2048, routed 256 and
+// 125 tokens on average (4600 and 2480 tiles against 5140 and 3070 of 128 x 128)
+// 177.5 -> 164.4 and 88.2 -> 82.4 us, NVFP4 190 -> 178; but 2048 x 768 at 256 tokens
+// (1730 against 1920) 163.9 -> 165.4 NVFP4, and 32 experts of 1536 x 2048 at 250
+// (1130 against 1280) 68 -> 76.
+static bool dx_wide_tiles(const GemmGroup& gg, const ExpertProblem* p, int n) {
+  int64_t wide = 0, square = 0;
+  for (int e = 0; e < n; ++e) {
+    wide += (p[e].T + 63) / 64;
+    square += (p[e].T + 127) / 128;
+  }
+  wide *= (gg.base.I + 255) / 256;
+  square *= (gg.base.I + 127) / 128;
+  return wide >= 6 * kCUs && wide * 10 <= square * 9;
+}
+
 // The large tile when the experts' tiles fill the chip and an expert averages
 // at least 512 tokens (rows of the forward and dX, the contraction of dS:
 // shorter token sums leave a 256 x 256 dS tile a few stages between its
@@ -1700,13 +1729,20 @@ static int grouped_sized(GemmGroup& gg, const ExpertProblem* p, int n, hipStream
   if (large) return launch_grouped<MODE, FMT, BM, BN, REST...>(gg, p, n, s);
   if constexpr (MODE == kFwdC) {
     if (tokens >= (int64_t)2048 * n) return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_FWDC_LONG>(gg, p, n, s);
+    if (tokens <= (int64_t)16 * n) return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_FEW_FWDC>(gg, p, n, s);
     return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_FWDC>(gg, p, n, s);
   }
   else if constexpr (MODE == kDs) return launch_ds_stream<FMT, SQ_CFG_DS_STREAM>(gg, p, n, s);
   else if constexpr (MODE == kDx) {
-    if (tokens <= (int64_t)96 * n) return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_THIN>(gg, p, n, s);
+    if (tokens <= (int64_t)16 * n) return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_FEW>(gg, p, n, s);
+    if (tokens <= (int64_t)96 * n || dx_wide_tiles(gg, p, n))
+      return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_THIN>(gg, p, n, s);
     return dx_split_tails<FMT>(gg, p, n, s);
-  } else return launch_grouped<MODE, FMT, SQ_CFG_SMALL>(gg, p, n, s);
+  } else {
+    if (tokens <= (int64_t)8 * n) return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_FEW>(gg, p, n, s);
+    if (tokens <= (int64_t)96 * n) return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_MID_FWDR>(gg, p, n, s);
+    return launch_grouped<MODE, FMT, SQ_CFG_SMALL>(gg, p, n, s);
+  }
 }
 
 template <int MODE>

@@ -1,7 +1,8 @@
 """Parity of the tiles that single products take when their grid leaves the
 chip idle: 64 x 64 and 64 x 128 (MXFP4 forward), 128 x 64 (NVFP4 forward), 64 x
 128 (dX), 256 x 128 (NVFP4 forward and dX) and 128 x 128 after a thin second
-round of large tiles.  Ragged in every dimension, on both sides of each limit,
+round of large tiles; and those of experts of a few tokens each, 32 x 128 and
+64 x 128.  Ragged in every dimension, on both sides of each limit,
 against the oracle per element; a grouped call of the same expert, whose tiles
 differ, gives the same bits."""
 
@@ -50,3 +51,27 @@ def test_parity_and_grouped_bits(sq, fmt, T, O, I):
     Yg = sq.sq_fwd_grouped(fmt, [Xc, Xc[:70]], [c, c], [s, s], [ws2, ws2])
     dXg = sq.sq_bwd_dx_grouped(fmt, [dYc, dYc[:70]], [c, c], [s, s], [ws2, ws2])
     assert torch.equal(Yg[0], Y) and torch.equal(dXg[0], dX)
+
+
+@pytest.mark.parametrize("fmt", ["mx", "nv"])
+@pytest.mark.parametrize("Ts,O,I", [
+    ([1, 0, 5, 33, 2, 7, 1], 136, 416),                    # 8 tokens on average and less: 32 x 128
+    ([32, 31, 1, 0, 64, 3, 1, 2], 264, 512),               # 16: the most for 32 x 128 forward (MXFP4) and dX
+    ([40, 65, 96, 1, 129, 30], 264, 528),                  # NVFP4 and 4-byte planes: 64 x 128
+])
+def test_few_tokens_per_expert(sq, fmt, Ts, O, I):
+    I -= I % 32 if fmt == "mx" else 0
+    L = [make_layer(fmt, T, O, I, seed=9800 + 7 * e) for e, T in enumerate(Ts)]
+    Xs, dYs = [x[0].cuda() for x in L], [x[1].cuda() for x in L]
+    cs, ss = [torch.from_numpy(x[2]).cuda() for x in L], [torch.from_numpy(x[3]).cuda() for x in L]
+    ws2 = [x[4] for x in L]
+    print(f"[few per expert] fmt={fmt} T={Ts} O={O} I={I}", flush=True)
+    for out in (torch.float32, torch.bfloat16):
+        Ys = sq.sq_fwd_grouped(fmt, Xs, cs, ss, ws2, out)
+        dXs = sq.sq_bwd_dx_grouped(fmt, dYs, cs, ss, ws2, out)
+        for e, T in enumerate(Ts):
+            if T:
+                assert torch.equal(Ys[e], sq.sq_fwd(fmt, Xs[e], cs[e], ss[e], ws2[e], out)), (e, T)
+                assert torch.equal(dXs[e], sq.sq_bwd_dx(fmt, dYs[e], cs[e], ss[e], ws2[e], out)), (e, T)
+            if out == torch.float32 and e in (0, 3):
+                check(fmt, *L[e], Ys[e].cpu().numpy(), dXs[e].cpu().numpy(), f"expert {e}")
