@@ -52,7 +52,7 @@ def kernel_source_digest():
     while the kernels they were taken on are unchanged."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("sq_gemm.hip", "sq_device.h"):
+    for f in ("sq_gemm.hip", "sq_gemm_args.h", "sq_thin.h", "sq_device.h"):
         with open(os.path.join(ROOT, "paper_2609_04526_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()

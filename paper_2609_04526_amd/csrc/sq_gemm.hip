@@ -12,8 +12,10 @@
 // All three feed v_mfma_f32_32x32x16_bf16 (fp32 accumulation) from LDS, in
 // K stages of 64, on 256 x 256 tiles of 8 waves (128 x 64 each in the MXFP4
 // forward, dX and dS; 64 x 128 in the LDS-dequantised forward) with two LDS
-// stages; grids that would leave CUs idle use 128 x 128 tiles, and a grid
-// ending in a short partial wave runs that remainder as half tiles.
+// stages; grids that would leave CUs idle use 128 x 128 or narrower tiles
+// (launch_sized), a grid ending in a short partial wave runs that remainder as
+// half tiles, and up to 64 tokens over a long contraction split that
+// contraction over a workgroup's waves (sq_thin.h).
 // How each operand reaches the matrix cores:
 //   * bf16 activations are copied global -> LDS by buffer loads that write LDS
 //     directly (no registers), with reads past the operand's end returning
