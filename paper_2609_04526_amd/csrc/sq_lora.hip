@@ -549,24 +549,39 @@ struct RedList {
 };
 static_assert(sizeof(RedList) <= 4096, "kernel argument budget");
 
+// Workgroups of an expert: 256 columns of one dA row each, then 256 consecutive
+// outputs of dB each.  One division per workgroup (and a 32-bit one per dB
+// output) instead of a 64-bit one per output: 4096 x 4096 at rank 32 6.6 -> 4.6
+// us, 32 experts of 768 x 2048 19.1 -> 16.3, at rank 50 29.8 -> 26.1.
+static __host__ __device__ inline int red_blocks_a(int r, int I) { return r * ((I + 255) / 256); }
+
 __global__ __launch_bounds__(256) void thin_m_reduce_kernel(RedList pl, int RW, int r, int I, int O, float c) {
   const int ei = find_product((int)blockIdx.x, pl.n, [&](int q) { return pl.p[q].blk0; });
   const RedProb& P = pl.p[ei];
-  const int64_t e = (int64_t)((int)blockIdx.x - P.blk0) * 256 + threadIdx.x;
-  const int64_t nA = (int64_t)r * I;
-  if (e < nA) {
-    const int j = (int)(e / I), i = (int)(e % I);
+  const int b = (int)blockIdx.x - P.blk0;
+  const int na = red_blocks_a(r, I);
+  if (b < na) {
+    const int segs = (I + 255) / 256;
+    const int j = b / segs, i = (b - j * segs) * 256 + (int)threadIdx.x;
+    if (i >= I) return;
+    const float* p = P.partA + (int64_t)j * I + i;
     float s = 0.0f;
-    for (int q = 0; q < P.splitsA; ++q) s += P.partA[((int64_t)q * RW + j) * I + i];
-    P.dA[e] = P.splitsA ? __fmul_rn(c, s) : 0.0f;
+#pragma unroll 4
+    for (int q = 0; q < P.splitsA; ++q) s += p[(int64_t)q * RW * I];
+    P.dA[(int64_t)j * I + i] = P.splitsA ? __fmul_rn(c, s) : 0.0f;
     return;
   }
-  const int64_t f = e - nA;
-  if (f >= (int64_t)r * O) return;
-  const int o = (int)(f / r), j = (int)(f % r);
+  const int64_t f0 = (int64_t)(b - na) * 256;
+  if (f0 + threadIdx.x >= (int64_t)r * O) return;
+  const int o0 = (int)(f0 / r);
+  const unsigned x = (unsigned)(f0 - (int64_t)o0 * r) + threadIdx.x;
+  const unsigned d = x / (unsigned)r;
+  const int o = o0 + (int)d, j = (int)(x - d * (unsigned)r);
+  const float* p = P.partB + (int64_t)o * RW + j;
   float s = 0.0f;
-  for (int q = 0; q < P.splitsB; ++q) s += P.partB[((int64_t)q * O + o) * RW + j];
-  P.dB[f] = P.splitsB ? __fmul_rn(c, s) : 0.0f;
+#pragma unroll 4
+  for (int q = 0; q < P.splitsB; ++q) s += p[(int64_t)q * O * RW];
+  P.dB[f0 + threadIdx.x] = P.splitsB ? __fmul_rn(c, s) : 0.0f;
 }
 
 // Bt[RW, O] = B[O, r]^T with rows r .. RW-1 zero, for the experts of a launch
@@ -703,7 +718,7 @@ static int lora_set(int e0, int n, const int64_t* T, int64_t tok0, int O, int I,
   RedList rl{};
   int nblk = 0, fblk = 0, mblk = 0, rblk = 0;
   int64_t tok = tok0;
-  const int red_per = (int)(((int64_t)r * (I + O) + 255) / 256);
+  const int red_per = red_blocks_a(r, I) + (int)(((int64_t)r * O + 255) / 256);
   for (int k = 0; k < n; ++k) {
     const int e = e0 + k;
     const int Te = (int)T[e];
