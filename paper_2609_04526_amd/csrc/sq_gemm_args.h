@@ -115,10 +115,12 @@ __device__ __forceinline__ DmaRsrc make_dma_rsrc(const void* p, uint32_t bytes) 
 // the instruction itself: the compiler's wait insertion cannot tell the LDS
 // tile a copy fills from the tile being read, and would otherwise stall
 // every later LDS read until the copy lands.  The loop waits for the copies
-// explicitly (vmcnt) before the barrier that publishes a stage.
+// explicitly (vmcnt) before the barrier that publishes a stage.  The s_nop is
+// the wait state that gfx9 needs between a write of M0 and a load to LDS; the
+// compiler does not look for hazards inside the block.
 __device__ __forceinline__ void dma16(DmaRsrc r, SQ_LDS void* dst, uint32_t voff) {
   const int lds = __builtin_amdgcn_readfirstlane((int)(uint32_t)reinterpret_cast<uintptr_t>(dst));
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(r.v)
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(r.v)
                : "memory", "m0");
 }
 
