@@ -98,10 +98,9 @@ typedef enum {
  * taken depends on the path: MXFP4 with codes 16-byte and scales 8-byte
  * aligned and I % 256 == 0 dequantises in registers (a lane takes 32
  * consecutive k), other
- * calls dequantise through LDS, so the two can differ in the last bits.  With
- * I > 2048, calls of up to 64 tokens split the contraction over 8 partial sums
- * that are added in a fixed order, so they can differ in the last bits from
- * the same rows of a longer call (sq_bwd_dx: likewise with O > 2048).
+ * calls dequantise through LDS, so the two can differ in the last bits.  It
+ * depends on nothing else: a row's result is the same bit for bit however many
+ * rows come with it (sq_bwd_dx: likewise, with one path).
  */
 int sq_fwd(int fmt, int64_t T, int64_t O, int64_t I,
            const void* X, const uint8_t* codes, const uint8_t* scales, float ws2,

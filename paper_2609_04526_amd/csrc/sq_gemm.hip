@@ -14,8 +14,8 @@
 // forward, dX and dS; 64 x 128 in the LDS-dequantised forward) with two LDS
 // stages; grids that would leave CUs idle use 128 x 128 or narrower tiles
 // (launch_sized), a grid ending in a short partial wave runs that remainder as
-// half tiles, and up to 64 tokens over a long contraction split that
-// contraction over a workgroup's waves (sq_thin.h).
+// half tiles, and up to 64 tokens over a long contraction take narrow strips
+// (sq_thin.h).
 // How each operand reaches the matrix cores:
 //   * bf16 activations are copied global -> LDS by buffer loads that write LDS
 //     directly (no registers), with reads past the operand's end returning
@@ -1460,63 +1460,111 @@ static bool regs_dequant_ok(int G, const ExpertProblem* p, int n) {
 }
 
 // ------------------------------------------------------------------ few tokens
-template <int FMT, int MT, int NT, int D>
-static int thin_fwd_go(const GemmArgs* one, GemmGroup* gg, hipStream_t s) {
-  if (one) {
-    const int tm = (one->T + 16 * MT - 1) / (16 * MT), tn = (one->O + 16 * NT - 1) / (16 * NT);
-    hipLaunchKernelGGL((thin_fwd_kernel<FMT, MT, NT, D>), dim3((unsigned)(tm * tn)), dim3(kThinThreads), 0, s, *one, tm);
-  } else {
-    int blocks = 0;
-    for (int e = 0; e < gg->count; ++e) {
-      gg->tile_begin[e] = blocks;
-      blocks += (gg->T[e] + 16 * MT - 1) / (16 * MT) * ((gg->base.O + 16 * NT - 1) / (16 * NT));
-    }
-    hipLaunchKernelGGL((thin_fwd_grouped_kernel<FMT, MT, NT, D>), dim3((unsigned)blocks), dim3(kThinThreads), 0, s, *gg);
-  }
-  return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-template <int FMT>
-static int thin_fwd(const GemmArgs* one, GemmGroup* gg, hipStream_t s) {
-  const ThinPick p = one ? thin_fwd_pick(FMT, &one->T, 1, one->O) : thin_fwd_pick(FMT, gg->T, gg->count, gg->base.O);
-  switch (p.mt * 10 + p.nt) {
-    case 11: return thin_fwd_go<FMT, 1, 1, 2>(one, gg, s);
-    case 12: return thin_fwd_go<FMT, 1, 2, 1>(one, gg, s);
-    case 14: return thin_fwd_go<FMT, 1, 4, 1>(one, gg, s);
-    case 21: return thin_fwd_go<FMT, 2, 1, 1>(one, gg, s);
-    case 22: return thin_fwd_go<FMT, 2, 2, 1>(one, gg, s);
-    case 24: return thin_fwd_go<FMT, 2, 4, 1>(one, gg, s);
-    case 41: return thin_fwd_go<FMT, 4, 1, 1>(one, gg, s);
-    case 42: return thin_fwd_go<FMT, 4, 2, 1>(one, gg, s);
-    default: return thin_fwd_go<FMT, 4, 4, 1>(one, gg, s);
-  }
-}
+// Calls of up to 64 tokens over more than 2048 terms take the strips of
+// sq_thin.h, which add in the tiles' order, so that the line between them is
+// a matter of time alone.  us at 4096 x 4096 / 14336 x 4096 / 4096 x 14336:
+//                     tiles               strips
+//   MXFP4 fwd T = 1   34.6 / 35.8 / 116   5.7 / 12.2 / 13.6
+//             T = 64  36.7 / 39.6 / 125   10.2 / 21.0 / 28.4
+//   NVFP4 fwd T = 1   37.0 / 41.2 / 134   5.9 / 12.4 / 13.9
+//             T = 48  38.5 / 45.9 / 148   9.8 / 17.0 / 26.8
+//   MXFP4 dX  T = 1   37.9 / 132 / 40.5   9.4 / 40.3 / 24.8
+//             T = 64  39.8 / 134 / 42.9   13.8 / 46.4 / 30.6
+// Sums as short as the 30B-A3B MoE's (768, 2048) stay on tiles.  Strips whose
+// eight waves each summed a part of the contraction took the MXFP4 forward 4.5
+// / 8.2 / 9.9 at T = 1 and 8.9 / 15.9 / 25.3 at 64, NVFP4 no less than these,
+// but their sums were others than the tiles', which bound an expert to the
+// path of its single call: 32 experts of 4096 x 4096 at 64 tokens 99 -> 150 us,
+// their dX 101 -> 288.
+constexpr int kThinTokens = 64, kThinK = 2048;
 
-// dX strips are 32 input features wide; their token tile follows the largest
-// token count (4096 x 4096 at 64 tokens 42.4 -> 14 us, 14336 x 4096 135 -> 41,
-// 4096 x 14336 43 -> 30; more tokens in flight per wave, D = 2, ran slower).
-template <int FMT, int MT>
-static int thin_dx_go(const GemmArgs* one, GemmGroup* gg, hipStream_t s) {
-  const int strips = ((one ? one->I : gg->base.I) + kThinDxCols - 1) / kThinDxCols;
+template <int MODE, int FMT, int MT, int NT, int KF, int D, int P>
+static int thin_go(const GemmArgs* one, GemmGroup* gg, hipStream_t s) {
+  const GemmArgs& g = one ? *one : gg->base;
+  const int strips = ((MODE == kThinFwd ? g.O : g.I) + 16 * NT - 1) / (16 * NT);
+  const dim3 block((unsigned)thin_threads<NT, KF>());
   if (one) {
     const int tm = (one->T + 16 * MT - 1) / (16 * MT);
-    hipLaunchKernelGGL((thin_dx_kernel<FMT, MT, 1>), dim3((unsigned)(tm * strips)), dim3(kThinThreads), 0, s, *one, tm);
+    hipLaunchKernelGGL((thin_kernel<MODE, FMT, MT, NT, KF, D, P>), dim3((unsigned)(tm * strips)), block, 0, s, *one, tm);
   } else {
     int blocks = 0;
     for (int e = 0; e < gg->count; ++e) {
       gg->tile_begin[e] = blocks;
       blocks += (gg->T[e] + 16 * MT - 1) / (16 * MT) * strips;
     }
-    hipLaunchKernelGGL((thin_dx_grouped_kernel<FMT, MT, 1>), dim3((unsigned)blocks), dim3(kThinThreads), 0, s, *gg);
+    hipLaunchKernelGGL((thin_grouped_kernel<MODE, FMT, MT, NT, KF, D, P>), dim3((unsigned)blocks), block, 0, s, *gg);
   }
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
+
+// Workgroups of strips of 16 mt tokens x 16 nt columns for products of T[0 ..
+// n-1] tokens and N columns.
+static int64_t thin_wgs(const int* T, int n, int N, int mt, int nt) {
+  int64_t w = 0;
+  for (int e = 0; e < n; ++e) w += (T[e] + 16 * mt - 1) / (16 * mt);
+  return w * ((N + 16 * nt - 1) / (16 * nt));
+}
+// Strip shapes of the forward, with the microseconds of one round (256
+// workgroups at most) at I = 4096: the shape of the least rounds times that.
+struct ThinShape {
+  int mt, nt;
+  double us;
+};
+static constexpr ThinShape kThinFwdShapes[] = {{1, 1, 5.8}, {1, 2, 7.6}, {2, 2, 9.9}, {1, 4, 12.3}, {2, 4, 14.3}, {3, 4, 17.5}, {4, 4, 20.3}};
+static ThinShape thin_fwd_shape(const int* T, int n, int O) {
+  ThinShape best{};
+  double best_us = 1e30;
+  for (const ThinShape& c : kThinFwdShapes) {
+    const double us = c.us * (double)((thin_wgs(T, n, O, c.mt, c.nt) + kCUs - 1) / kCUs);
+    if (us < best_us) {
+      best_us = us;
+      best = c;
+    }
+  }
+  return best;
+}
+// dX strips are 32 columns; the fewest token tiles that hold the most tokens,
+// but two of 32 while both fit the CUs (4096 x 4096 at 64 tokens 13.8 us, one
+// of 64 14.4).
+static ThinShape thin_dx_shape(const int* T, int n, int I) {
+  int most = 0;
+  for (int e = 0; e < n; ++e) most = T[e] > most ? T[e] : most;
+  if (most <= 16) return {1, 2, 0};
+  if (most <= 32 || thin_wgs(T, n, I, 2, 2) <= kCUs) return {2, 2, 0};
+  return {most <= 48 ? 3 : 4, 2, 0};
+}
+// dX strips read 16 bytes of every row of W, so that lines cross the caches
+// once per strip and XCD: past two workgroups per CU tiles are the faster
+// (4096 x 28672 at 16 tokens 44 us, 52 on strips; at 64 46 and 59).
+static bool thin_dx_fits(const int* T, int n, int I) {
+  const ThinShape c = thin_dx_shape(T, n, I);
+  return thin_wgs(T, n, I, c.mt, c.nt) <= 2 * kCUs;
+}
+
+template <int FMT>
+static int thin_fwd(const GemmArgs* one, GemmGroup* gg, hipStream_t s) {
+  const ThinShape c = one ? thin_fwd_shape(&one->T, 1, one->O) : thin_fwd_shape(gg->T, gg->count, gg->base.O);
+  switch (10 * c.mt + c.nt) {
+    case 11: return thin_go<kThinFwd, FMT, 1, 1, 16, 3, 4>(one, gg, s);
+    case 12: return thin_go<kThinFwd, FMT, 1, 2, 8, 4, 4>(one, gg, s);
+    case 22: return thin_go<kThinFwd, FMT, 2, 2, 8, 3, 4>(one, gg, s);
+    case 14: return thin_go<kThinFwd, FMT, 1, 4, 4, 4, 8>(one, gg, s);
+    case 24: return thin_go<kThinFwd, FMT, 2, 4, 4, 4, 4>(one, gg, s);
+    case 34: return thin_go<kThinFwd, FMT, 3, 4, 4, 4, 4>(one, gg, s);
+    default: return thin_go<kThinFwd, FMT, 4, 4, 4, 4, 4>(one, gg, s);
+  }
+}
 template <int FMT>
 static int thin_dx(const GemmArgs* one, GemmGroup* gg, hipStream_t s) {
-  int most = one ? one->T : 0;
-  for (int e = 0; gg && e < gg->count; ++e) most = gg->T[e] > most ? gg->T[e] : most;
-  if (most <= 16) return thin_dx_go<FMT, 1>(one, gg, s);
-  if (most <= 32) return thin_dx_go<FMT, 2>(one, gg, s);
-  return thin_dx_go<FMT, 4>(one, gg, s);
+  const ThinShape c = one ? thin_dx_shape(&one->T, 1, one->I) : thin_dx_shape(gg->T, gg->count, gg->base.I);
+  switch (c.mt) {
+    case 1:
+      if constexpr (FMT == kMX) return thin_go<kThinDx, FMT, 1, 2, 8, 3, 4>(one, gg, s);
+      else return thin_go<kThinDx, FMT, 1, 2, 4, 4, 4>(one, gg, s);
+    case 2: return thin_go<kThinDx, FMT, 2, 2, 8, 3, 4>(one, gg, s);
+    case 3: return thin_go<kThinDx, FMT, 3, 2, 4, 4, 4>(one, gg, s);
+    default: return thin_go<kThinDx, FMT, 4, 2, 4, 4, 4>(one, gg, s);
+  }
 }
 
 // ------------------------------------------------------------------ entry
@@ -1529,13 +1577,15 @@ int gemm_fwd(int fmt, int T, int O, int I, const void* X, const uint8_t* codes,
   g.M = T; g.N = O; g.K = I;
   g.ws2 = (fmt == kNV) ? ws2 : 1.0f;
   g.out_bf16 = y_bf16;
-  // registers dequantise when the code and scale planes are 16-byte aligned
-  // and every row's scales split into 16-byte runs
-  if (thin_takes(T, I)) return fmt == kMX ? thin_fwd<kMX>(&g, nullptr, s) : thin_fwd<kNV>(&g, nullptr, s);
+  // tiles dequantise in registers when the code and scale planes are 16-byte
+  // aligned and every row's scales split into 16-byte runs; strips follow the
+  // order of the tiles that the call would have taken
   ExpertProblem one{};
   one.codes = codes;
   one.scales = scales;
-  if (fmt == kMX && regs_dequant_ok(g.G, &one, 1)) return launch_sized<kFwdC, kMX, SQ_CFG_FWDC>(g, s);
+  g.reg_order = fmt == kMX && regs_dequant_ok(g.G, &one, 1);
+  if (T <= kThinTokens && I > kThinK) return fmt == kMX ? thin_fwd<kMX>(&g, nullptr, s) : thin_fwd<kNV>(&g, nullptr, s);
+  if (g.reg_order) return launch_sized<kFwdC, kMX, SQ_CFG_FWDC>(g, s);
   return fmt == kMX ? launch_sized<kFwdR, kMX, SQ_CFG_FWD>(g, s) : launch_sized<kFwdR, kNV, SQ_CFG_FWD>(g, s);
 }
 
@@ -1548,7 +1598,8 @@ int gemm_dx(int fmt, int T, int O, int I, const void* dY, const uint8_t* codes,
   g.M = T; g.N = I; g.K = O;
   g.ws2 = (fmt == kNV) ? ws2 : 1.0f;
   g.out_bf16 = dx_bf16;
-  if (thin_takes(T, O)) return fmt == kMX ? thin_dx<kMX>(&g, nullptr, s) : thin_dx<kNV>(&g, nullptr, s);
+  if (T <= kThinTokens && O > kThinK && thin_dx_fits(&T, 1, I))
+    return fmt == kMX ? thin_dx<kMX>(&g, nullptr, s) : thin_dx<kNV>(&g, nullptr, s);
   return fmt == kMX ? launch_sized<kDx, kMX, SQ_CFG_DX>(g, s) : launch_sized<kDx, kNV, SQ_CFG_DX>(g, s);
 }
 
@@ -1678,15 +1729,26 @@ static int dx_split_tails(GemmGroup& gg, const ExpertProblem* p, int n, hipStrea
   return launch_grouped<kDx, FMT, SQ_CFG_GROUPED_THIN>(gt, tail, nt, s);
 }
 
+// Strips for a grouped call whose experts all have few tokens while its strips
+// leave the chip idle or nearly so: up to two workgroups per CU, the MXFP4
+// forward one.  A full chip does better on tiles, which spend less on each
+// weight they read: us, 4 / 8 / 32 experts of 4096 x 4096, 24 tokens each, tiles
+// against strips: MXFP4 forward 36 / 36 / 76, 17 / 31 / 123; NVFP4 38 / 41 / 130,
+// 16 / 30 / 135; MXFP4 dX 49 / 50 / 85, 28 / 51 / 208.  Between one and two
+// workgroups per CU the MXFP4 forward is about even (8 experts of 4096 x 4096
+// at 8 tokens 25.0 against 27.3, at 64 tokens 36 against 43).
 template <int MODE, int FMT>
-static int grouped_thin(GemmGroup& gg, const ExpertProblem* p, int n, hipStream_t s) {
+static bool grouped_thin(GemmGroup& gg, const ExpertProblem* p, int n) {
+  if (gg.base.K <= kThinK) return false;
   gg.count = n;
   for (int e = 0; e < n; ++e) {
+    if (p[e].T > kThinTokens) return false;
     gg.T[e] = p[e].T;
     gg.ws2[e] = FMT == kNV ? p[e].ws2 : 1.0f;
   }
-  if constexpr (MODE == kDx) return thin_dx<FMT>(nullptr, &gg, s);
-  else return thin_fwd<FMT>(nullptr, &gg, s);
+  if constexpr (MODE == kDx) return thin_dx_fits(gg.T, n, gg.base.I);
+  const ThinShape c = thin_fwd_shape(gg.T, n, gg.base.O);
+  return thin_wgs(gg.T, n, gg.base.O, c.mt, c.nt) <= (FMT == kMX ? 1 : 2) * kCUs;
 }
 
 // Grouped dX over many tiles takes 64 x 256 throughout where its finer token
@@ -1710,27 +1772,12 @@ static bool dx_wide_tiles(const GemmGroup& gg, const ExpertProblem* p, int n) {
 // at least 512 tokens (rows of the forward and dX, the contraction of dS:
 // shorter token sums leave a 256 x 256 dS tile a few stages between its
 // prologue and epilogue, where two 128 x 128 workgroups per CU do better).
-// Experts that take the few-token kernels (as their single calls do) run in a
-// launch of their own.
 template <int MODE, int FMT, int BM, int BN, int... REST>
 static int grouped_sized(GemmGroup& gg, const ExpertProblem* p, int n, hipStream_t s) {
-  ExpertProblem sub[kGroupMax];
-  if constexpr (MODE != kDs) {
-    int few = 0;
-    for (int e = 0; e < n; ++e)
-      if (thin_takes(p[e].T, gg.base.K)) sub[few++] = p[e];
-    if (few == n) return grouped_thin<MODE, FMT>(gg, p, n, s);
-    if (few > 0) {
-      if (!set_experts(gg, sub, few, false)) return -1;       // a part of a set that fits
-      const int rc = grouped_thin<MODE, FMT>(gg, sub, few, s);
-      if (rc != 0) return rc;
-      int m = 0;
-      for (int e = 0; e < n; ++e)
-        if (!thin_takes(p[e].T, gg.base.K)) sub[m++] = p[e];
-      if (!set_experts(gg, sub, m, false)) return -1;
-      p = sub;
-      n = m;
-    }
+  if constexpr (MODE == kDx) {
+    if (grouped_thin<MODE, FMT>(gg, p, n)) return thin_dx<FMT>(nullptr, &gg, s);
+  } else if constexpr (MODE != kDs) {
+    if (grouped_thin<MODE, FMT>(gg, p, n)) return thin_fwd<FMT>(nullptr, &gg, s);
   }
   int64_t tokens = 0, big = 0;
   for (int e = 0; e < n; ++e) {
@@ -1774,6 +1821,7 @@ static int run_grouped(int fmt, int O, int I, int n, const ExpertProblem* p, int
   // experts of a stacked tensor, or of one allocator pool, share a set; an
   // expert's results do not depend on the set it runs in).
   const bool regs = MODE == kFwdR && fmt == kMX && regs_dequant_ok(gg.base.G, p, n);
+  gg.base.reg_order = regs;
   std::vector<uint8_t> done((size_t)n, 0);
   ExpertProblem set[kGroupMax];
   for (int first = 0; first < n;) {

@@ -29,6 +29,7 @@ struct GemmArgs {
   int T, O, I, G;
   float ws2;              // NV epilogue factor (1 for MX)
   int out_bf16;
+  int reg_order;          // few-token forward: sum in the order of the register path (kFwdC)
   int ksplit;             // DS: K (token) ranges per tile; >1 writes partial planes to `out`
   int ksteps_per;         // DS: K stages per range
   // the launch covers output rows [m_off, m_off + m_cnt) and columns
@@ -121,6 +122,12 @@ __device__ __forceinline__ DmaRsrc make_dma_rsrc(const void* p, uint32_t bytes) 
 __device__ __forceinline__ void dma16(DmaRsrc r, SQ_LDS void* dst, uint32_t voff) {
   const int lds = __builtin_amdgcn_readfirstlane((int)(uint32_t)reinterpret_cast<uintptr_t>(dst));
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(r.v)
+               : "memory", "m0");
+}
+// 4 bytes per lane; lane l writes dst + 4 l.
+__device__ __forceinline__ void dma4(DmaRsrc r, SQ_LDS void* dst, uint32_t voff) {
+  const int lds = __builtin_amdgcn_readfirstlane((int)(uint32_t)reinterpret_cast<uintptr_t>(dst));
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(r.v)
                : "memory", "m0");
 }
 
