@@ -1354,20 +1354,26 @@ static int launch_gemm(const GemmArgs& g, hipStream_t s) {
 // per-element sums are the same in every configuration, so results do not
 // depend on the choice); a stage's round trip, not its work, sets the pace
 // there, and more and smaller workgroups per CU overlap more of them.  By the
-// number n of 128 x 128 tiles, measured at K = 4096 and 14336, us:
-//   MXFP4 forward  n <= 192: 64 x 64, 4 waves, four stages (40 KiB: four per
-//                  CU): n = 32 38.0 -> 25.1, 128 40.6 -> 29.2, 192 42.1 -> 36.7;
-//                  n <= 352: 64 x 128, 4 waves: n = 224 42.8 -> 38.0, 352 57.3
-//                  -> 54.3 (448: 59.3 either way)
-//   NVFP4 forward  n <= 256: 128 x 64: n = 64 46.4 -> 34.0, 128 46.1 -> 34.3,
-//                  256 49.9 -> 48.9
-//   dX             n <= 128: 64 x 128: n = 32 43.3 -> 36.1, 128 42.9 -> 38.2
-//                  (192: 45.0 -> 49.2)
+// number n of 128 x 128 tiles, as a share of those tiles' time over random T, N
+// and K = 512 to 14336 (and us at K = 4096):
+//   MXFP4 forward  n <= 160: 64 x 64, 4 waves, four stages (40 KiB: four per
+//                  CU): 0.65-0.82 up to n = 128, 0.92-0.97 to 150, 1.02-1.06 at
+//                  180-192 (n = 32 38.0 -> 25.1, 128 40.6 -> 29.2);
+//                  n <= 352: 64 x 128, 4 waves: 0.87-0.99 (n = 224 42.8 -> 38.0,
+//                  352 57.3 -> 54.3), but not for 232 < n <= 256, which 128 x
+//                  128 tiles fill in one round (1.02-1.09), nor above that over
+//                  more than 4096 terms (320 at K = 14336 1.05)
+//   NVFP4 forward  n <= 128: 128 x 64: 0.67-0.86 (n = 64 46.4 -> 34.0, 128 46.1 ->
+//                  34.3); from 130 on 0.91-1.05
+//   dX             n <= 128: 64 x 128: 0.76-0.90 (n = 32 43.3 -> 36.1, 128 42.9 ->
+//                  38.2); from 130 on 1.02-1.19
 // Above those, the NVFP4 forward and dX over at least 2048 terms take 256 x 128
 // tiles where they fill their rounds (one round at least 0.7 full, or two
-// 0.85): 4096 x 4096 at 1999 tokens (256 of them) 79.7 -> 73.4 and 72.2 -> 63.6,
-// 1400 tokens (192) 69.5 -> 66.8 and 64.7 -> 58.2, but 3000 tokens (384) 120 ->
-// 133 and 106 -> 117; dX over 1024 terms 23.4 -> 25.0.
+// 0.85) and their rows are at most a tenth more than those of 128-row tiles:
+// 4096 x 4096 at 1999 tokens (256 of them) 79.7 -> 73.4 and 72.2 -> 63.6, 1400
+// tokens (192) 69.5 -> 66.8 and 64.7 -> 58.2, but 3000 tokens (384) 120 -> 133 and
+// 106 -> 117; dX over 1024 terms 23.4 -> 25.0; 4104 x 12272 at 346 tokens (512
+// rows of tiles for 384) 74.9 -> 77.7.
 #define SQ_CFG_FEW_FWDC 64, 64, 2, 2, 4, 64
 #define SQ_CFG_MID_FWDC 64, 128, 1, 4, 4, 64
 #define SQ_CFG_FEW_FWDR 128, 64, 4, 2, 2, 64
@@ -1394,16 +1400,17 @@ static int launch_sized(const GemmArgs& g, hipStream_t s) {
   if (MODE != kDs && BM == 256 && BN == 256) {
     const int64_t n = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128);
     if constexpr (MODE == kFwdC) {
-      if (n <= 192) return launch_gemm<MODE, FMT, SQ_CFG_FEW_FWDC>(g, s);
-      if (n <= 352) return launch_gemm<MODE, FMT, SQ_CFG_MID_FWDC>(g, s);
+      if (n <= 160) return launch_gemm<MODE, FMT, SQ_CFG_FEW_FWDC>(g, s);
+      if (n <= 232 || (n > kCUs && n <= 352 && g.K <= 4096)) return launch_gemm<MODE, FMT, SQ_CFG_MID_FWDC>(g, s);
     } else if constexpr (MODE == kFwdR) {
-      if (n <= 256) return launch_gemm<MODE, FMT, SQ_CFG_FEW_FWDR>(g, s);
+      if (n <= 128) return launch_gemm<MODE, FMT, SQ_CFG_FEW_FWDR>(g, s);
     } else if constexpr (MODE == kDx) {
       if (n <= 128) return launch_gemm<MODE, FMT, SQ_CFG_FEW_DX>(g, s);
     }
     if constexpr (MODE == kFwdR || MODE == kDx) {
       const int64_t half = (int64_t)tm * ((g.N + 127) / 128), rounds = (half + kCUs - 1) / kCUs;
-      if (big < kCUs && n > 256 && g.K >= 2048 && half * 100 >= (rounds == 1 ? 70 : 85) * rounds * kCUs)
+      if (big < kCUs && n > kCUs && g.K >= 2048 && half * 100 >= (rounds == 1 ? 70 : 85) * rounds * kCUs &&
+          half * 20 <= n * 11)
         return launch_gemm<MODE, FMT, SQ_CFG_HALF_N>(g, s);
     }
   }

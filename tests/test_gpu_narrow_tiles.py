@@ -30,13 +30,25 @@ def tiles(M, N):
 SHAPES = [
     ("mx", 65, 72, 256), ("nv", 65, 72, 272),              # one tile, one row over 64
     ("mx", 193, 200, 1024), ("nv", 193, 200, 528),
-    ("mx", 1500, 2040, 256), ("mx", 1540, 2056, 256),       # 192 and 221 tiles: 64 x 64, 64 x 128
+    ("mx", 1270, 2040, 256), ("mx", 1290, 2040, 256),       # 160 and 176 tiles: 64 x 64, 64 x 128
+    ("mx", 1020, 3704, 256), ("mx", 1540, 2440, 256),       # 232 and 260: 64 x 128
+    ("mx", 1020, 3720, 256), ("mx", 2030, 2040, 256),       # 240 and 256: 128 x 128
     ("mx", 2800, 2040, 256), ("mx", 2820, 2056, 256),       # 352 and 391: 64 x 128, 128 x 128
-    ("nv", 2030, 2040, 272), ("nv", 2050, 2056, 272),       # 256 and 289 tiles
+    ("nv", 1020, 2040, 272), ("nv", 1030, 2056, 272),       # 128 and 153: 128 x 64, 128 x 128
     ("mx", 1000, 264, 2040 // 32 * 32), ("nv", 1030, 264, 2032),   # dX: 128 tiles and more
     ("nv", 2040, 4104, 2064), ("mx", 1290, 2056, 4128),     # 256 x 128 tiles over long sums
+    ("nv", 346, 12296, 2064), ("mx", 346, 2056, 12320),     # not where they would be a third padding
     ("mx", 1290, 14344, 64), ("nv", 1290, 14344, 64),       # 342 large tiles: a thin second round
 ]
+
+
+def test_the_limits_are_on_both_sides():
+    n = {f"{fmt} fwd": sorted(tiles(T, O) for f, T, O, I in SHAPES if f == fmt) for fmt in ("mx", "nv")}
+    for at in (160, 176, 232, 240, 256, 260, 352, 391):
+        assert at in n["mx fwd"], at
+    assert {128, 153} <= set(n["nv fwd"])
+    dx = {tiles(T, I) for f, T, O, I in SHAPES}
+    assert 128 in dx and any(128 < t < 160 for t in dx)
 
 
 @pytest.mark.parametrize("fmt,T,O,I", SHAPES)
