@@ -1663,13 +1663,20 @@ static int launch_ds_stream(GemmGroup& gg, const ExpertProblem* p, int n, hipStr
 #define SQ_CFG_GROUPED_THIN 64, 256, 1, 8, 2, 64
 // Experts of a few tokens each (a serving batch over an MoE layer) are bound by
 // the weights' round trips and their padding: 32 x 128 tiles, 4 waves, so that
-// four to six workgroups share a CU.  128 experts of 768 x 2048, us, at 1, 4
-// and 12 tokens on average: MXFP4 forward 23.5, 32.8, 33.8 -> 17.4, 23.4, 30.4
-// (31 tokens: 36.6 -> 37.9); dX 28.6, 36.3, 35.7 -> 21.5, 28.3, 33.2 (44.5 ->
-// 41.5, but 2048 x 768 42.8 -> 47.4): up to 16 tokens.  NVFP4 forward 38.9, 55.5
-// -> 26.0, 34.8, and from 12 tokens on 64 x 128 is the faster: 58.0 -> 41.3, 31
-// tokens 60.6 -> 55.7, 62 tokens 74.3 -> 66.9 (125: 99 -> 105): 32 x 128 up to 8,
-// 64 x 128 up to 96.
+// four workgroups share a CU, for up to 16 tokens on average where no expert has
+// more than 32 (else a second row of tiles reads its weights again) or, for the
+// forward, the tiles fit two to a CU.  128 experts of 768 x 2048, us, at 1, 4 and 12
+// tokens on average: MXFP4 forward 23.5, 32.8, 33.8 -> 17.4, 23.4, 30.4 (31 tokens:
+// 36.6 -> 37.9); dX 28.6, 36.3, 35.7 -> 21.5, 28.3, 33.2; 64 experts of 1536 x 2048
+// at 16 tokens, some of them over 32: dX 41.4 -> 53.2.  dX tiles of 128 columns read
+// 64 bytes of a row of W, which from memory is slower than 128 where the rows are
+// long and the chip full: 32 experts of 4096 x 4096 at 8 tokens 86 -> 102, 8 of them
+// 64 -> 57.  So dX takes them for I <= 2304 or where they fit one to a CU.
+// NVFP4 forward 38.9, 55.5 -> 26.0, 34.8 with 32 x 128 up to 8 tokens (no worse with
+// experts over 32), and with 64 x 128 up to 96, where those hold at most 1.4 times
+// the tiles of 128 rows or fit one to a CU: 12 tokens 58.0 -> 41.3, 31 60.6 -> 55.7,
+// 62 74.3 -> 66.9; at 80 to 96 tokens routed unevenly, 1.5 to 1.6 times the tiles,
+// 0.86 to 1.3 of the time, by how the rounds end.
 #define SQ_CFG_GROUPED_FEW_FWDC 32, 128, 1, 4, 4, 64
 #define SQ_CFG_GROUPED_FEW 32, 128, 1, 4, 2, 64
 #define SQ_CFG_GROUPED_MID_FWDR 64, 128, 2, 4, 2, 64
@@ -1786,28 +1793,35 @@ static int grouped_sized(GemmGroup& gg, const ExpertProblem* p, int n, hipStream
   } else if constexpr (MODE != kDs) {
     if (grouped_thin<MODE, FMT>(gg, p, n)) return thin_fwd<FMT>(nullptr, &gg, s);
   }
-  int64_t tokens = 0, big = 0;
+  int64_t tokens = 0, big = 0, rows32 = 0, rows64 = 0, rows128 = 0;     // rows: of tiles
   for (int e = 0; e < n; ++e) {
     tokens += p[e].T;
+    rows32 += (p[e].T + 31) / 32;
+    rows64 += (p[e].T + 63) / 64;
+    rows128 += (p[e].T + 127) / 128;
     const int M = MODE == kDs ? gg.base.M : p[e].T;
     big += (int64_t)((M + BM - 1) / BM) * ((gg.base.N + BN - 1) / BN);
   }
   const bool large = big >= kCUs && tokens >= (int64_t)512 * n;
   if (large) return launch_grouped<MODE, FMT, BM, BN, REST...>(gg, p, n, s);
+  const int64_t cols = (gg.base.N + 127) / 128;
   if constexpr (MODE == kFwdC) {
     if (tokens >= (int64_t)2048 * n) return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_FWDC_LONG>(gg, p, n, s);
-    if (tokens <= (int64_t)16 * n) return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_FEW_FWDC>(gg, p, n, s);
+    if (tokens <= (int64_t)16 * n && (rows32 == rows64 || rows32 * cols <= 2 * kCUs))
+      return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_FEW_FWDC>(gg, p, n, s);
     return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_FWDC>(gg, p, n, s);
   }
   else if constexpr (MODE == kDs) return launch_ds_stream<FMT, SQ_CFG_DS_STREAM>(gg, p, n, s);
   else if constexpr (MODE == kDx) {
-    if (tokens <= (int64_t)16 * n) return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_FEW>(gg, p, n, s);
+    if (tokens <= (int64_t)16 * n && rows32 == rows64 && (gg.base.I <= 2304 || rows32 * cols <= kCUs))
+      return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_FEW>(gg, p, n, s);
     if (tokens <= (int64_t)96 * n || dx_wide_tiles(gg, p, n))
       return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_THIN>(gg, p, n, s);
     return dx_split_tails<FMT>(gg, p, n, s);
   } else {
     if (tokens <= (int64_t)8 * n) return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_FEW>(gg, p, n, s);
-    if (tokens <= (int64_t)96 * n) return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_MID_FWDR>(gg, p, n, s);
+    if (tokens <= (int64_t)96 * n && (rows64 * 5 <= rows128 * 7 || rows64 * cols <= kCUs))
+      return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_MID_FWDR>(gg, p, n, s);
     return launch_grouped<MODE, FMT, SQ_CFG_SMALL>(gg, p, n, s);
   }
 }

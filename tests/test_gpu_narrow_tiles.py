@@ -65,19 +65,59 @@ def test_parity_and_grouped_bits(sq, fmt, T, O, I):
     assert torch.equal(Yg[0], Y) and torch.equal(dXg[0], dX)
 
 
+def grouped_tile(kind, fmt, Ts, O, I):
+    """The tile that a grouped call of few-token experts takes (csrc/sq_gemm.hip, grouped_sized)."""
+    Ts = [T for T in Ts if T]                              # empty experts are left out before
+    n, N = len(Ts), O if kind == "fwd" else I
+    r32, r64, r128 = (sum(-(-T // r) for T in Ts) for r in (32, 64, 128))
+    cols = -(-N // 128)
+    if kind == "dx":
+        few = sum(Ts) <= 16 * n and r32 == r64 and (I <= 2304 or r32 * cols <= 256)
+        return "32x128" if few else "64x256" if sum(Ts) <= 96 * n else None
+    if fmt == "mx" and I % 256 == 0:                       # registers dequantise
+        return "32x128" if sum(Ts) <= 16 * n and (r32 == r64 or r32 * cols <= 512) else "64x256"
+    if sum(Ts) <= 8 * n:
+        return "32x128"
+    return "64x128" if sum(Ts) <= 96 * n and (5 * r64 <= 7 * r128 or r64 * cols <= 256) else "128x128"
+
+
+# (experts' tokens, O, I, forward tile MXFP4, NVFP4, dX tile)
+FEW = [
+    ([1, 0, 5, 33, 2, 7, 0], 136, 416, "64x128", "64x128", "64x256"),        # 9.6 tokens an expert, one over 32
+    ([1, 5, 31, 2, 7, 2, 8], 264, 512, "32x128", "32x128", "32x128"),        # exactly 8, registers (MXFP4)
+    ([1, 5, 32, 2, 7, 2, 8], 264, 512, "32x128", "64x128", "32x128"),        # one token more
+    ([3, 0, 9, 12, 8], 264, 528, "32x128", "32x128", "32x128"),              # exactly 8, through LDS
+    ([32, 32, 1, 2, 30, 4, 11], 264, 512, "32x128", "64x128", "32x128"),     # exactly 16, the most
+    ([32, 32, 1, 2, 30, 4, 12], 264, 512, "64x256", "64x128", "64x256"),     # one token more
+    ([33, 30, 1, 2, 30, 4, 12], 264, 512, "32x128", "64x128", "64x256"),     # 16, one expert over 32: few tiles
+    ([33, 1, 2, 1] * 32, 520, 256, "64x256", "64x128", "64x256"),            # the same where they fill the chip
+    ([1, 5, 31, 2, 7, 2, 8], 136, 416, "32x128", "32x128", "32x128"),        # exactly 8, MXFP4 through LDS
+    ([3, 1, 2, 1] * 16, 96, 2560, None, None, "64x256"),                     # dX over long rows, 1280 tiles (forward: strips)
+    ([40, 65, 96, 1, 129, 30], 264, 528, "64x256", "64x128", "64x256"),
+    ([96, 90, 100, 98], 264, 528, "64x256", "64x128", "64x256"),             # exactly 96: 64 x 128 one to a CU
+    ([96, 90, 100, 99], 264, 528, "64x256", "128x128", None),
+    ([100, 90, 80, 70] * 16, 1032, 80, "128x128", "128x128", "64x256"),      # 64-row tiles twice the 128-row ones
+]
+
+
+def test_the_few_token_tiles_are_all_taken():
+    for Ts, O, I, mx, nv, dx in FEW:
+        Im = I - I % 32
+        assert I > 2048 or (grouped_tile("fwd", "mx", Ts, O, Im), grouped_tile("fwd", "nv", Ts, O, I)) == (mx, nv), Ts
+        assert grouped_tile("dx", "mx", Ts, O, Im) == grouped_tile("dx", "nv", Ts, O, I) == dx, Ts
+    assert {(mx, (I - I % 32) % 256 == 0) for _, _, I, mx, _, _ in FEW} >= {("32x128", True), ("64x256", True), ("32x128", False), ("64x128", False)}
+
+
 @pytest.mark.parametrize("fmt", ["mx", "nv"])
-@pytest.mark.parametrize("Ts,O,I", [
-    ([1, 0, 5, 33, 2, 7, 1], 136, 416),                    # 8 tokens on average and less: 32 x 128
-    ([32, 31, 1, 0, 64, 3, 1, 2], 264, 512),               # 16: the most for 32 x 128 forward (MXFP4) and dX
-    ([40, 65, 96, 1, 129, 30], 264, 528),                  # NVFP4 and 4-byte planes: 64 x 128
-])
+@pytest.mark.parametrize("Ts,O,I", [c[:3] for c in FEW], ids=lambda v: str(v)[:24])
 def test_few_tokens_per_expert(sq, fmt, Ts, O, I):
     I -= I % 32 if fmt == "mx" else 0
     L = [make_layer(fmt, T, O, I, seed=9800 + 7 * e) for e, T in enumerate(Ts)]
     Xs, dYs = [x[0].cuda() for x in L], [x[1].cuda() for x in L]
     cs, ss = [torch.from_numpy(x[2]).cuda() for x in L], [torch.from_numpy(x[3]).cuda() for x in L]
     ws2 = [x[4] for x in L]
-    print(f"[few per expert] fmt={fmt} T={Ts} O={O} I={I}", flush=True)
+    print(f"[few per expert] fmt={fmt} T={Ts[:8]} O={O} I={I} fwd {grouped_tile('fwd', fmt, Ts, O, I)} "
+          f"dx {grouped_tile('dx', fmt, Ts, O, I)}", flush=True)
     for out in (torch.float32, torch.bfloat16):
         Ys = sq.sq_fwd_grouped(fmt, Xs, cs, ss, ws2, out)
         dXs = sq.sq_bwd_dx_grouped(fmt, dYs, cs, ss, ws2, out)
@@ -85,5 +125,5 @@ def test_few_tokens_per_expert(sq, fmt, Ts, O, I):
             if T:
                 assert torch.equal(Ys[e], sq.sq_fwd(fmt, Xs[e], cs[e], ss[e], ws2[e], out)), (e, T)
                 assert torch.equal(dXs[e], sq.sq_bwd_dx(fmt, dYs[e], cs[e], ss[e], ws2[e], out)), (e, T)
-            if out == torch.float32 and e in (0, 3):
+            if out == torch.float32 and T and e < 8:
                 check(fmt, *L[e], Ys[e].cpu().numpy(), dXs[e].cpu().numpy(), f"expert {e}")
