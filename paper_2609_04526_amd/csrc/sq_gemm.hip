@@ -1766,12 +1766,19 @@ static bool grouped_thin(GemmGroup& gg, const ExpertProblem* p, int n) {
 }
 
 // Grouped dX over many tiles takes 64 x 256 throughout where its finer token
-// tiles leave a tenth of the work out: 128 experts of 768 x 2048, routed 256 and
-// 125 tokens on average (4600 and 2480 tiles against 5140 and 3070 of 128 x 128)
-// 177.5 -> 164.4 and 88.2 -> 82.4 us, NVFP4 190 -> 178; but 2048 x 768 at 256 tokens
-// (1730 against 1920) 163.9 -> 165.4 NVFP4, and 32 experts of 1536 x 2048 at 250
-// (1130 against 1280) 68 -> 76.
-static bool dx_wide_tiles(const GemmGroup& gg, const ExpertProblem* p, int n) {
+// tiles leave enough of the work out to make up for reading each weight twice
+// as often, which they do over short contractions only.  Share of the time of 128
+// x 128 tiles (with short last tiles as below) by the rows of 64 x 256 tiles over
+// those of 128 x 128, from 1536 tiles on, 64 to 128 routed experts of 110 to 400
+// tokens on average:
+//   O = 768, 1024  MXFP4 0.87-0.96 up to 0.90, 0.95-0.99 at 0.91-0.92, 1.03 at 0.93;
+//                  NVFP4 0.82-0.98 up to 0.86, 0.95-1.01 to 0.90, 1.00-1.03 above
+//   O = 1536       0.88-1.01 up to 0.86, 0.96-1.07 above
+//   O = 2048       1.01-1.11 at 0.85-0.93
+// An even share of 256 tokens an expert, as 4096 tokens over 8 of 128 experts
+// give, lies at 0.88 to 0.92 by the noise of the routing, well to one side of the
+// line at O = 768 (MXFP4 187 -> 177 us at 0.91; NVFP4 about even either way).
+static bool dx_wide_tiles(int fmt, const GemmGroup& gg, const ExpertProblem* p, int n) {
   int64_t wide = 0, square = 0;
   for (int e = 0; e < n; ++e) {
     wide += (p[e].T + 63) / 64;
@@ -1779,7 +1786,8 @@ static bool dx_wide_tiles(const GemmGroup& gg, const ExpertProblem* p, int n) {
   }
   wide *= (gg.base.I + 255) / 256;
   square *= (gg.base.I + 127) / 128;
-  return wide >= 6 * kCUs && wide * 10 <= square * 9;
+  const int most = gg.base.O > 1536 ? 0 : gg.base.O > 1024 || fmt == kNV ? 86 : 93;   // hundredths
+  return wide >= 6 * kCUs && wide * 100 <= square * most;
 }
 
 // The large tile when the experts' tiles fill the chip and an expert averages
@@ -1815,7 +1823,7 @@ static int grouped_sized(GemmGroup& gg, const ExpertProblem* p, int n, hipStream
   else if constexpr (MODE == kDx) {
     if (tokens <= (int64_t)16 * n && rows32 == rows64 && (gg.base.I <= 2304 || rows32 * cols <= kCUs))
       return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_FEW>(gg, p, n, s);
-    if (tokens <= (int64_t)96 * n || dx_wide_tiles(gg, p, n))
+    if (tokens <= (int64_t)96 * n || dx_wide_tiles(FMT, gg, p, n))
       return launch_grouped<MODE, FMT, SQ_CFG_GROUPED_THIN>(gg, p, n, s);
     return dx_split_tails<FMT>(gg, p, n, s);
   } else {

@@ -270,33 +270,47 @@ def test_moe_layer_shapes_sampled(sq):
         # token sum whole (here: fewer than 8 token stages, T <= 448)
         compared = sum(single_dscale_equal(sq, "mx", Xd[e], dYd[e], cd[e], dSs[e]) for e in range(E))
         assert compared >= sum(T <= 448 for T in Ts)
-        # every expert's dX equals its single product bit for bit; for the
-        # gate shape the experts whose last 128-token tile would hold 64 rows
-        # or fewer run those rows in a second launch of 64 x 256 tiles
-        if I == 2048:
-            assert dx_tail_split_taken(Ts, I)
+        # every expert's dX equals its single product bit for bit; the gate
+        # shape takes 64 x 256 tiles throughout
+        assert dx_wide_taken("mx", O, I, Ts) == (I == 2048)
         for e in range(E):
             one = sq.sq_bwd_dx("mx", dYd[e], cd[e], sd[e])
             assert torch.equal(one, dXs[e]), (O, I, e, Ts[e])
 
 
-def test_grouped_dx_tail_split_nvfp4_bf16(sq):
-    """Grouped NVFP4 dX with bf16 outputs over the routed split of a MoE
-    layer (gate shape), where the short last token tiles run in a second
-    launch: every expert's dX equals its single product bit for bit."""
-    E, O, I = 128, 768, 2048
+@pytest.mark.parametrize("fmt,O,I,E,rows,route", [
+    ("nv", 768, 2048, 128, 4096 * 8, "split"),   # 256 tokens an expert: NVFP4 splits the short last tiles off
+    ("mx", 1536, 2048, 64, 190 * 64, "whole"),
+    ("mx", 768, 2048, 64, 125 * 64, "whole"),    # too few tiles for 64 x 256
+    ("nv", 768, 2048, 128, 125 * 128, "wide"),
+    ("mx", 768, 2048, 128, 125 * 128, "wide"),
+    ("mx", 1536, 2048, 100, 130 * 100, "wide"),
+])
+def test_grouped_dx_routes_bf16(sq, fmt, O, I, E, rows, route):
+    """Grouped dX with bf16 outputs over routed splits of MoE layers: 64 x 256
+    tiles throughout, 128 x 128 throughout, or the short last token tiles of
+    those in a second launch of 64 x 256; every expert's dX equals its single product bit for bit."""
     g = inputs.rng(7650)
-    Ts = g.multinomial(4096 * 8, g.dirichlet(np.full(E, 2.0))).tolist()
-    assert dx_tail_split_taken(Ts, I)
-    codes, scales, ws2 = experts("nv", E, O, I, 7660)
+    Ts = g.multinomial(rows, g.dirichlet(np.full(E, 2.0))).tolist()
+    taken = "wide" if dx_wide_taken(fmt, O, I, Ts) else "split" if dx_tail_split_taken(Ts, I) else "whole"
+    assert sum(Ts) > 96 * sum(T > 0 for T in Ts) and taken == route
+    codes, scales, ws2 = experts(fmt, E, O, I, 7660)
     cd, sd = cuda(codes), cuda(scales)
     dYd = [inputs.device_bf16_normal(7670 + e, (T, O)) for e, T in enumerate(Ts)]
-    print(f"[moe dx split] nv bf16 O={O} I={I} experts={E} tokens={sum(Ts)}", flush=True)
-    dXs = sq.sq_bwd_dx_grouped("nv", dYd, cd, sd, ws2, out_dtype=torch.bfloat16)
+    print(f"[moe dx route] {fmt} bf16 O={O} I={I} experts={E} tokens={sum(Ts)} {route}", flush=True)
+    dXs = sq.sq_bwd_dx_grouped(fmt, dYd, cd, sd, ws2, out_dtype=torch.bfloat16)
     torch.cuda.synchronize()
     for e in range(E):
-        one = sq.sq_bwd_dx("nv", dYd[e], cd[e], sd[e], ws2[e], out_dtype=torch.bfloat16)
+        one = sq.sq_bwd_dx(fmt, dYd[e], cd[e], sd[e], ws2[e], out_dtype=torch.bfloat16)
         assert torch.equal(one, dXs[e]), (e, Ts[e])
+
+
+def dx_wide_taken(fmt, O, I, Ts, cus=256):
+    """Whether grouped dX takes 64 x 256 tiles throughout (csrc/sq_gemm.hip, dx_wide_tiles)."""
+    wide = sum((T + 63) // 64 for T in Ts) * ((I + 255) // 256)
+    square = sum((T + 127) // 128 for T in Ts) * ((I + 127) // 128)
+    most = 0 if O > 1536 else 86 if O > 1024 or fmt == "nv" else 93
+    return wide >= 6 * cus and wide * 100 <= square * most
 
 
 def dx_tail_split_taken(Ts, I, cus=256):
