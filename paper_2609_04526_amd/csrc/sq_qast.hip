@@ -23,6 +23,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "sq_device.h"
 #include "sq_grid.h"
 #include "sq_launch.h"
@@ -39,91 +41,146 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // plane where there is nothing to load, and their values dropped afterwards
 // (a branch per load made each wait for the one before).  blockIdx.y is the
 // expert: rows e O .. e O + O - 1 of base, B, out and mask belong to it, its A
-// is A + e r G and its ws2 ws2.v[e].  The MFMA's rows are scale blocks g and
-// its columns output rows o, so a lane ends with four consecutive bytes of one
-// row: with vec (G % 4 == 0 and 4-byte aligned byte planes) one word each way.
+// is A + e r G and its ws2 ws2.v[e].  With vec (G % 4 == 0 and 4-byte aligned
+// byte planes) the MFMA's rows are scale blocks g and its columns output rows o,
+// so that a lane ends with four consecutive bytes of one row, one word each
+// way.  Else its operands change places: a lane ends with one byte of each of
+// four rows, and 16 lanes with 16 consecutive bytes of a row (14336 x 129 at
+// rank 58, NVFP4: 26.8 -> 17.3 us, 128 experts of 1536 x 65 at rank 2 54.2 -> 36.2,
+// against vector multiply-adds fed from LDS).
 
-// The four scales of row o from block g on, whose delta sums are s[0..3].
+// The sums s[0..3] of a lane to scales: blocks g .. g + 3 of row o (vec), or
+// block g of rows o .. o + 3.  The base bytes come from base4 of the same place.
 template <int FMT>
 __device__ __forceinline__ void scale4(const float (&s)[4], const uint32_t (&in)[4], float c, const Ws2Div& wd,
-                                       uint8_t* out, uint8_t* mask, size_t at, int left, int vec) {
-  uint32_t nw = 0, mw = 0;
+                                       uint8_t* out, uint8_t* mask, size_t rows0, int o, int g, int O, int G,
+                                       int vec) {
+  uint32_t n[4], m[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     bool clamped;
-    nw |= grid_update<FMT>(in[j], __fmul_rn(s[j], c), wd, clamped) << (8 * j);
-    mw |= (clamped ? 0u : 1u) << (8 * j);
+    n[j] = grid_update<FMT>(in[j], __fmul_rn(s[j], c), wd, clamped);
+    m[j] = clamped ? 0u : 1u;
   }
+  if (o >= O || g >= G) return;
+  const size_t at = (rows0 + o) * G + g;
   if (vec) {
-    *reinterpret_cast<uint32_t*>(out + at) = nw;
-    if (mask) *reinterpret_cast<uint32_t*>(mask + at) = mw;
+    *reinterpret_cast<uint32_t*>(out + at) = n[0] | (n[1] << 8) | (n[2] << 16) | (n[3] << 24);
+    if (mask) *reinterpret_cast<uint32_t*>(mask + at) = m[0] | (m[1] << 8) | (m[2] << 16) | (m[3] << 24);
   } else {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      if (j >= left) break;
-      out[at + j] = (uint8_t)(nw >> (8 * j));
-      if (mask) mask[at + j] = (uint8_t)((mw >> (8 * j)) & 1u);
+      if (o + j >= O) break;
+      out[at + (size_t)j * G] = (uint8_t)n[j];
+      if (mask) mask[at + (size_t)j * G] = (uint8_t)m[j];
     }
   }
 }
-__device__ __forceinline__ void base4(uint32_t (&in)[4], const uint8_t* base, size_t at, size_t inside, bool ok,
-                                      int left, int vec) {
+__device__ __forceinline__ void base4(uint32_t (&in)[4], const uint8_t* base, size_t rows0, int o, int g, int O, int G,
+                                      int vec) {
+  const size_t inside = rows0 * G, at = (rows0 + o) * G + g;
+  const bool ok = o < O && g < G;
   if (vec) {
     const uint32_t w = *reinterpret_cast<const uint32_t*>(base + (ok ? at : inside));
 #pragma unroll
     for (int j = 0; j < 4; ++j) in[j] = (w >> (8 * j)) & 0xFFu;
   } else {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) in[j] = base[ok && j < left ? at + j : inside];
+    for (int j = 0; j < 4; ++j) in[j] = base[ok && o + j < O ? at + (size_t)j * G : inside];
   }
 }
+
+// n consecutive bf16 values (a workgroup's rows of a factor are one run of
+// memory) to LDS, w of them per load (w = 8 or 2: their place and n allow it),
+// and the RMAX x COLS tile of A at block g0 (zeros past r and G).
+__device__ __forceinline__ void stage_run(uint16_t* dst, const uint16_t* __restrict__ src, int n, int w) {
+  auto copy = [&](auto Z) {
+    typedef decltype(Z) V;
+    const V* s = reinterpret_cast<const V*>(src);
+    const int m = n / (int)(sizeof(V) / 2);
+    for (int i = threadIdx.x; i < m; i += 1024) {
+      V v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = s[i + 256 * u < m ? i + 256 * u : 0];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (i + 256 * u < m) reinterpret_cast<V*>(dst)[i + 256 * u] = v[u];
+    }
+  };
+  if (w == 8) copy(uint4{});
+  else if (w == 2) copy(uint32_t{});
+  else copy(uint16_t{});
+}
+template <int RMAX, int COLS>
+struct ATile {
+  static constexpr int kPer = (RMAX * COLS + 255) / 256;
+  uint16_t v[kPer];
+  __device__ __forceinline__ void load(const uint16_t* __restrict__ ap, int g0, int G, int r) {
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int i = threadIdx.x + 256 * u, k = i / COLS, g = g0 + i % COLS;
+      v[u] = ap[k < r && g < G ? (size_t)k * G + g : 0];
+    }
+  }
+  __device__ __forceinline__ void store(uint16_t (*lds)[COLS], int g0, int G, int r) const {
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int i = threadIdx.x + 256 * u, k = i / COLS, g = g0 + i % COLS;
+      if (RMAX * COLS < 256 && k >= RMAX) break;
+      lds[k][i % COLS] = k < r && g < G ? v[u] : (uint16_t)0;
+    }
+  }
+};
 
 // One linear: latency is what bounds it, so a wave takes a single 16 x 16
 // block and four ranks per MFMA (v_mfma_f32_16x16x4 adds its four terms in
 // increasing k, each with its own rounding: every byte the tests compare
 // depends on it).  GB of a workgroup's four waves lie along g, the rest along
-// o.  4096 x 256 scales at rank 58: 12.2 us on vector multiply-adds fed from
-// LDS, 9.4 here; 4096 x 128 at rank 32 6.6 -> 5.8.
+// o.  A workgroup's rows of B and columns of A come through LDS, since a load
+// per rank and lane cost more than the products from rank 32 on (4096 x 256 at
+// rank 64 11.8 us so, 8.8 through LDS).  4096 x 256 scales at rank 58, NVFP4: 10.1
+// us on vector multiply-adds fed from LDS, 7.3 here; 4096 x 293 8.3 -> 7.1 at rank
+// 26, 7384 x 77 5.7 -> 5.2 at rank 11.
 template <int FMT, int RMAX, int GB>
 __global__ __launch_bounds__(256, 4) void qast_scales_kernel(const uint8_t* __restrict__ base,
                                                           const uint16_t* __restrict__ B,
                                                           const uint16_t* __restrict__ A, int O, int G, int r,
                                                           float c, Ws2Table ws2, uint8_t* out, uint8_t* mask,
-                                                          int vec) {
+                                                          int vec, int w) {
+  constexpr int COLS = 16 * GB, ROWS = 64 / GB;
+  __shared__ uint16_t at_lds[RMAX][COLS];
+  __shared__ __attribute__((aligned(16))) uint16_t b_lds[ROWS * RMAX];
   const int e = blockIdx.y;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4;
-  const int gtiles = (G + 16 * GB - 1) / (16 * GB);
-  const int g0 = ((int)blockIdx.x % gtiles * GB + wave % GB) * 16;
-  const int o0 = ((int)blockIdx.x / gtiles * (4 / GB) + wave / GB) * 16;
-  if (o0 >= O || g0 >= G) return;
+  const int gtiles = (G + COLS - 1) / COLS;
+  const int gw = (int)blockIdx.x % gtiles * COLS, ow = (int)blockIdx.x / gtiles * ROWS;   // of the workgroup
+  const int g0 = gw + wave % GB * 16, ro = wave / GB * 16, o0 = ow + ro;
   const size_t rows0 = (size_t)e * O;
-  const bool g_ok = g0 + n < G, o_ok = o0 + n < O;
-  const uint16_t* ap = A + (size_t)e * r * G + (g_ok ? g0 + n : 0);
-  const uint16_t* bp = B + (rows0 + (o_ok ? o0 + n : 0)) * r;
-  uint16_t ar[RMAX / 4], br[RMAX / 4];
-#pragma unroll
-  for (int st = 0; st < RMAX / 4; ++st) {
-    const int k = 4 * st + q, kc = k < r ? k : 0;
-    ar[st] = ap[(size_t)kc * G];
-    br[st] = bp[kc];
-  }
-  const int g = g0 + 4 * q;
-  const size_t at = (rows0 + o0 + n) * G + g;
+  ATile<RMAX, COLS> at;
+  at.load(A + (size_t)e * r * G, gw, G, r);
+  stage_run(b_lds, B + (rows0 + ow) * r, min(ROWS, O - ow) * r, w);
+  const int g = vec ? g0 + 4 * q : g0 + n, o = vec ? o0 + n : o0 + 4 * q;
   uint32_t in[4];
-  base4(in, base, at, rows0 * G, o_ok && g < G, G - g, vec);
+  base4(in, base, rows0, o, g, O, G, vec);
+  at.store(at_lds, gw, G, r);
   const Ws2Div wd = make_ws2_div(ws2.v[e]);
+  __syncthreads();
+  const bool o_ok = o0 + n < O;
+  const uint16_t* bl = b_lds + (o_ok ? (ro + n) * r : 0);
   f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+  auto multiply = [&](auto VEC) {
 #pragma unroll
-  for (int st = 0; st < RMAX / 4; ++st) {
-    const bool in_r = 4 * st + q < r;                    // ranks past r add exact zeros
-    const float av = g_ok && in_r ? bf16_bits_to_f32(ar[st]) : 0.0f;
-    const float bv = o_ok && in_r ? bf16_bits_to_f32(br[st]) : 0.0f;
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc, 0, 0, 0);
-  }
-  if (o_ok && g < G) {
-    const float sum[4] = {acc[0], acc[1], acc[2], acc[3]};
-    scale4<FMT>(sum, in, c, wd, out, mask, at, G - g, vec);
-  }
+    for (int st = 0; st < RMAX / 4; ++st) {
+      const int k = 4 * st + q;                          // ranks past r add exact zeros
+      const float av = bf16_bits_to_f32(at_lds[k][wave % GB * 16 + n]);
+      const float bv = o_ok && k < r ? bf16_bits_to_f32(bl[k < r ? k : 0]) : 0.0f;
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(VEC ? av : bv, VEC ? bv : av, acc, 0, 0, 0);
+    }
+  };
+  if (vec) multiply(std::true_type{});
+  else multiply(std::false_type{});
+  const float sum[4] = {acc[0], acc[1], acc[2], acc[3]};
+  scale4<FMT>(sum, in, c, wd, out, mask, rows0, o, g, O, G, vec);
 }
 
 // Many scales (stacked experts, the widest linears): the address unit bounds
@@ -131,79 +188,77 @@ __global__ __launch_bounds__(256, 4) void qast_scales_kernel(const uint8_t* __re
 // (v_mfma_f32_16x16x1: a register of A and one of B per rank serve all four),
 // GB of them along g; the workgroup's waves lie below one another and share
 // the A columns, of which each loads a quarter of the ranks into LDS; a row
-// of B comes W ranks per load.  128 experts of 768 x 128 scales at rank 54
-// (NVFP4): 82 us on vector multiply-adds fed from LDS, 57 with A loaded by
-// every wave, 50 now.
-template <int FMT, int RMAX, int GB, int W>
+// of B comes W ranks per load or, at odd ranks and where VEC is off, through
+// LDS, since the rows of a workgroup are one run of memory (16 experts of 1536 x
+// 64 at rank 31, NVFP4: 8.1 us, 9.0 on vector multiply-adds).  128 experts of
+// 768 x 128 scales at rank 58 (NVFP4): 85 us on vector multiply-adds fed from
+// LDS, 44 here, at rank 64 86 -> 34; at rank 5, where the bytes bound it, 20.9 ->
+// 22.1.  VEC is a parameter: with both orders of the operands in one kernel the
+// compiler spilled (77 us instead of 29 for 128 experts of 2048 x 24 at rank 58).
+template <int FMT, int RMAX, int GB, int W, bool VEC>
 __global__ __launch_bounds__(256, 4) void qast_scales_wide_kernel(const uint8_t* __restrict__ base,
                                                                const uint16_t* __restrict__ B,
                                                                const uint16_t* __restrict__ A, int O, int G, int r,
                                                                float c, Ws2Table ws2, uint8_t* out, uint8_t* mask,
-                                                               int vec) {
-  constexpr int OB = 4 / GB, COLS = 16 * GB;
+                                                               int w) {
+  constexpr int OB = 4 / GB, COLS = 16 * GB, ROWS = 64 * OB;
   __shared__ uint16_t at_lds[RMAX][COLS];
+  __shared__ __attribute__((aligned(16))) uint16_t b_lds[W == 1 ? ROWS * RMAX : 8];
   const int e = blockIdx.y;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4;
   const int gtiles = (G + COLS - 1) / COLS;
   const int g0 = ((int)blockIdx.x % gtiles) * COLS;
-  const int o0 = (((int)blockIdx.x / gtiles) * 4 + wave) * 16 * OB;
+  const int ow = ((int)blockIdx.x / gtiles) * ROWS, ro = wave * 16 * OB, o0 = ow + ro;
   const size_t rows0 = (size_t)e * O;
-  const uint16_t* ap = A + (size_t)e * r * G;
-  constexpr int kPer = (RMAX * COLS + 255) / 256;
-  uint16_t av16[kPer];
+  ATile<RMAX, COLS> at;
+  at.load(A + (size_t)e * r * G, g0, G, r);
+  if constexpr (W == 1) stage_run(b_lds, B + (rows0 + ow) * r, min(ROWS, O - ow) * r, w);
+  const int rl = 16 * (q / GB) + n;                     // this lane's operand row
+  const bool o_ok = o0 + rl < O;
+  uint32_t br[W > 1 ? RMAX / 2 : 1];                    // pairs of ranks
+  if constexpr (W > 1) {
+    const uint16_t* bp = B + (rows0 + (o_ok ? o0 + rl : 0)) * r;
 #pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-    const int i = threadIdx.x + 256 * u, k = i / COLS, g = g0 + i % COLS;
-    av16[u] = ap[k < r && g < G ? (size_t)k * G + g : 0];
-  }
-  const int ol = o0 + 16 * (q / GB) + n;                // this lane's operand row
-  const bool o_ok = ol < O;
-  const uint16_t* bp = B + (rows0 + (o_ok ? ol : 0)) * r;
-  uint32_t br[RMAX / 2];                                // pairs of ranks
-#pragma unroll
-  for (int k = 0; k < RMAX; k += W > 1 ? W : 2) {
-    const int kc = k < r ? k : 0;                       // r is a multiple of W
-    if constexpr (W == 8) {
-      const uint4 v = *reinterpret_cast<const uint4*>(bp + kc);
-      br[k / 2] = v.x; br[k / 2 + 1] = v.y; br[k / 2 + 2] = v.z; br[k / 2 + 3] = v.w;
-    } else if constexpr (W == 2) {
-      br[k / 2] = *reinterpret_cast<const uint32_t*>(bp + kc);
-    } else {
-      br[k / 2] = (uint32_t)bp[kc] | ((uint32_t)bp[k + 1 < r ? k + 1 : 0] << 16);
+    for (int k = 0; k < RMAX; k += W) {
+      const int kc = k < r ? k : 0;                     // r is a multiple of W
+      if constexpr (W == 8) {
+        const uint4 v = *reinterpret_cast<const uint4*>(bp + kc);
+        br[k / 2] = v.x; br[k / 2 + 1] = v.y; br[k / 2 + 2] = v.z; br[k / 2 + 3] = v.w;
+      } else {
+        br[k / 2] = *reinterpret_cast<const uint32_t*>(bp + kc);
+      }
     }
   }
-  // the result: block b, register 4 b + j is row g0 + 16 (b % GB) + 4 q + j of
-  // column o0 + 16 (b / GB) + n
+  // the result: block b, register 4 b + j is MFMA row 4 q + j, column n.  With VEC
+  // the MFMA's row 4 q + j of block b is scale block g0 + 4 GB q + 4 (b % GB) + j, so
+  // that a lane's GB words of a row lie side by side; else rows and columns are
+  // output rows and scale blocks in their order.
+  auto row = [&](int b) { return o0 + 16 * (b / GB) + (VEC ? n : 4 * q); };
+  auto blk = [&](int b) { return g0 + (VEC ? 4 * GB * q + 4 * (b % GB) : 16 * (b % GB) + n); };
+  const int acol = VEC ? 4 * GB * (n >> 2) + 4 * (q % GB) + (n & 3) : 16 * (q % GB) + n;
   uint32_t in[4][4];
 #pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    const int o = o0 + 16 * (b / GB) + n, g = g0 + 16 * (b % GB) + 4 * q;
-    base4(in[b], base, (rows0 + o) * G + g, rows0 * G, o < O && g < G, G - g, vec);
-  }
-#pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-    const int i = threadIdx.x + 256 * u, k = i / COLS, g = g0 + i % COLS;
-    if (RMAX * COLS < 256 && k >= RMAX) break;
-    at_lds[k][i % COLS] = k < r && g < G ? av16[u] : (uint16_t)0;     // ranks past r add exact zeros
-  }
+  for (int b = 0; b < 4; ++b) base4(in[b], base, rows0, row(b), blk(b), O, G, VEC);
+  at.store(at_lds, g0, G, r);
   __syncthreads();
+  const uint16_t* bl = b_lds + (W == 1 && o_ok ? (ro + rl) * r : 0);
   f32x16 acc;
 #pragma unroll
   for (int j = 0; j < 16; ++j) acc[j] = 0.0f;
 #pragma unroll
   for (int k = 0; k < RMAX; ++k) {
-    const uint32_t bw = k & 1 ? br[k / 2] & 0xFFFF0000u : br[k / 2] << 16;
-    const float av = bf16_bits_to_f32(at_lds[k][16 * (q % GB) + n]);
+    uint32_t bw;
+    if constexpr (W == 1) bw = (uint32_t)bl[k < r ? k : 0] << 16;
+    else bw = k & 1 ? br[k / 2] & 0xFFFF0000u : br[k / 2] << 16;
+    const float av = bf16_bits_to_f32(at_lds[k][acol]);
     const float bv = o_ok && k < r ? __uint_as_float(bw) : 0.0f;
-    acc = __builtin_amdgcn_mfma_f32_16x16x1f32(av, bv, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x1f32(VEC ? av : bv, VEC ? bv : av, acc, 0, 0, 0);
   }
   const Ws2Div wd = make_ws2_div(ws2.v[e]);
 #pragma unroll
   for (int b = 0; b < 4; ++b) {
-    const int o = o0 + 16 * (b / GB) + n, g = g0 + 16 * (b % GB) + 4 * q;
-    if (o >= O || g >= G) continue;
     const float sum[4] = {acc[4 * b], acc[4 * b + 1], acc[4 * b + 2], acc[4 * b + 3]};
-    scale4<FMT>(sum, in[b], c, wd, out, mask, (rows0 + o) * G + g, G - g, vec);
+    scale4<FMT>(sum, in[b], c, wd, out, mask, rows0, row(b), blk(b), O, G, VEC);
   }
 }
 
@@ -245,13 +300,13 @@ template <int U>
 __device__ __forceinline__ void load_v(float (&v)[U], const float* __restrict__ dS, const uint8_t* __restrict__ mask,
                                        int O, int G, int o, int g, int vec) {
   const size_t row = o < O ? (size_t)o * G : 0;
-  if (vec) {
+  if (U > 1 && vec) {
     const size_t at_ = row + (g < G ? g : 0);
     if constexpr (U == 4) {
       const f32x4 w = *reinterpret_cast<const f32x4*>(dS + at_);
 #pragma unroll
       for (int j = 0; j < U; ++j) v[j] = w[j];
-    } else {
+    } else if constexpr (U == 2) {
       const f32x2 w = *reinterpret_cast<const f32x2*>(dS + at_);
       v[0] = w[0];
       v[1] = w[1];
@@ -360,7 +415,12 @@ __device__ __forceinline__ void da_tile(int bx, int e, float* lds, const float* 
 #pragma unroll
   for (int st = 0; st < 4; ++st) {
     const int o = o0 + 4 * st + q, k0 = RT * n;
-    load_v<U>(v[st], dS, mask, O, G, o, g0 + U * n, vec);
+    if (vec) {
+      load_v<U>(v[st], dS, mask, O, G, o, g0 + U * n, vec);
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u) load_v<1>(*reinterpret_cast<float (*)[1]>(&v[st][u]), dS, mask, O, G, o, g0 + 16 * u + n, 0);
+    }
     const uint16_t* bp = B + (o < O ? (size_t)o * r : 0);
     if (RT > 1 && bvec) {                               // r even, B 4-byte aligned: pairs of ranks
 #pragma unroll
@@ -387,7 +447,7 @@ __device__ __forceinline__ void da_tile(int bx, int e, float* lds, const float* 
   // and 3 park their sums, waves 0 and 1 add theirs (half the LDS of four
   // planes, so twice the workgroups per CU), then the two planes are added.
   auto at = [&](int w, int t, int x, int u) -> float& {
-    return lds[(w * 16 * RT + RT * (4 * q + x) + t) * S + U * n + u];
+    return lds[(w * 16 * RT + RT * (4 * q + x) + t) * S + (vec ? U * n + u : 16 * u + n)];
   };
   if (wave >= 2) {
 #pragma unroll
@@ -470,16 +530,19 @@ static void scales_go(bool wide, int w, int64_t gtiles, int m, hipStream_t s, co
   const int rows = (wide ? 4 : 1) * 16 * (4 / GB);                   // of a workgroup
   const dim3 grid((unsigned)(((O + rows - 1) / rows) * gtiles), (unsigned)m);
   if (!wide)
-    hipLaunchKernelGGL((qast_scales_kernel<F, R, GB>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op, mp, vec);
+    hipLaunchKernelGGL((qast_scales_kernel<F, R, GB>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op, mp, vec, w);
+  else if (!vec)
+    hipLaunchKernelGGL((qast_scales_wide_kernel<F, R, GB, 1, false>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op,
+                       mp, w);
   else if (w == 8)
-    hipLaunchKernelGGL((qast_scales_wide_kernel<F, R, GB, 8>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op, mp,
-                       vec);
+    hipLaunchKernelGGL((qast_scales_wide_kernel<F, R, GB, 8, true>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op,
+                       mp, w);
   else if (w == 2)
-    hipLaunchKernelGGL((qast_scales_wide_kernel<F, R, GB, 2>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op, mp,
-                       vec);
+    hipLaunchKernelGGL((qast_scales_wide_kernel<F, R, GB, 2, true>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op,
+                       mp, w);
   else
-    hipLaunchKernelGGL((qast_scales_wide_kernel<F, R, GB, 1>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op, mp,
-                       vec);
+    hipLaunchKernelGGL((qast_scales_wide_kernel<F, R, GB, 1, true>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op,
+                       mp, w);
 }
 template <int F, int R>
 static void scales_gb(bool wide, int gb, int w, int m, hipStream_t s, const uint8_t* bp, const uint16_t* Bp,

@@ -220,17 +220,10 @@ def test_batched_experts_match_per_expert(sq, fmt, E, O, G, r):
         assert normwise(dB[e].cpu().numpy(), wB) <= TOL and normwise(dA[e].cpu().numpy(), wA) <= TOL
 
 
-def _rmax(r):
-    return 8 if r <= 8 else 16 if r <= 16 else 32 if r <= 32 else 64
-
-
-def wide_tiles_taken(E, O, G, r, cus=256):
-    """Whether a batched call of this shape runs the wide tiles: the scale step's
-    128-row x 32-block tiles and the dB pass's 4 rows per thread, each chosen
-    when it still gives every CU two workgroups."""
-    scales = E * -(-O // 128) * -(-G // 32) >= 2 * cus
-    db_rows = 4 * (256 // (_rmax(r) // 4))
-    return scales and E * -(-O // db_rows) >= 2 * cus
+def wide_tiles_taken(E, O, G):
+    """Whether a batched call of this shape runs the scale step's wide tiles: four
+    16 x 16 blocks per wave, from 6144 such blocks on."""
+    return E * -(-O // 16) * -(-G // 16) >= 6144
 
 
 @pytest.mark.parametrize("fmt,E,O,G,r", [("mx", 130, 520, 40, 32), ("nv", 130, 520, 37, 33)])
@@ -241,7 +234,7 @@ def test_batched_wide_tiles(sq, fmt, E, O, G, r):
     expert's bytes, mask and gradients equal the single-plane calls' (narrow
     tiles) bit for bit, and sampled experts equal the oracle."""
     print(f"[qast wide] fmt={fmt} E={E} O={O} G={G} r={r}", flush=True)
-    assert wide_tiles_taken(E, O, G, r) and not wide_tiles_taken(1, O, G, r)
+    assert wide_tiles_taken(E, O, G) and not wide_tiles_taken(1, O, G)
     bases, ws2s, Bs, As = [], [], [], []
     for e in range(E):
         base, ws2 = plane(fmt, O, G, 8100 + e)
