@@ -954,8 +954,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bid, int nb) {
     // The compiler cannot see the copies in flight, so where it waits for a
     // chunk of scales it waits for all of them.  Here, before this stage's
     // copy goes out, the youngest is a stage old; at the chunk's first use it
-    // would have been the one just issued (the routed MoE layer's step 505 ->
-    // 502 us, the 1024 x 4096 forward at 1999 tokens 1% less).
+    // would have been the one just issued.  1024 x 4096 at 1999 tokens 34.1 us
+    // there, 32.4 here; 4096 x 4096 at 1000 tokens 47.8, 44.1; 128 experts of
+    // 768 x 2048 over 16,384 rows 79.0, 75.1; from 4096 rows of 4096 x 4096 on
+    // the same.
     if constexpr (MODE == kFwdC && STAGES > 2) {
       if ((kt & 7) == 7) {
 #pragma unroll
