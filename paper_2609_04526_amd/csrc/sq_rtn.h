@@ -87,6 +87,29 @@ __device__ __forceinline__ uint32_t e2m1_rtz_code(float q) {
 // sweep).
 enum : int { kRuleEven = 0, kRuleAway = 1, kRuleRtz = 2, kRuleStochastic = 3, kRuleWholeTensor = 4 };
 
+// fp32(amax / 6) through the reciprocal of 6: correctly rounded for every
+// bf16 amax at or above 2^-120 (all 31,744 of them were checked against
+// true division with an exact emulation); smaller, zero and NaN divide.
+__device__ __forceinline__ float sixth_of(float amax) {
+  return amax >= 0x1p-120f ? div_exact<1>(amax, RcpDivisor{6.0f, 0x1.555556p-3f, true}) : __fdiv_rn(amax, 6.0f);
+}
+
+// MXFP4: the scale byte k + 127 of a block whose amax / 6 is `sixth`, and 2^-k as
+// fp32 (exact: 2^-127 is subnormal, 2^127 normal), NaN for a NaN block.
+__device__ __forceinline__ uint32_t mx_scale_byte(float sixth, float* inv) {
+  if (sixth != sixth) {
+    *inv = __uint_as_float(0x7FC00000u);
+    return 0xFFu;
+  }
+  int k;
+  if (sixth == 0.0f) k = -127;
+  else if (sixth > 3.4028234e38f) k = 127;
+  else k = ceil_log2_pos(sixth);
+  k = k < -127 ? -127 : (k > 127 ? 127 : k);
+  *inv = (k == 127) ? __uint_as_float(0x00400000u) : __uint_as_float((uint32_t)(127 - k) << 23);
+  return (uint32_t)(k + 127);
+}
+
 // One chunk of 8 consecutive weights of a row (16 bytes of bf16, already
 // loaded); the B/8 lanes of a block are adjacent and share the block amax.
 // amax_t: the tensor amax (whole-tensor rule); seed: the Philox key
@@ -124,29 +147,12 @@ __device__ __forceinline__ void rtn_chunk(const uint4 v, int64_t c, bool valid, 
     if (LPB == 4) am = max(am, (uint32_t)__shfl_xor((int)am, 2));
   }
   const float amax = __uint_as_float(am << 16);
-  // fp32(amax / 6) through the reciprocal of 6: correctly rounded for every
-  // bf16 amax at or above 2^-120 (all 31,744 of them were checked against
-  // true division with an exact emulation); smaller, zero and NaN divide
-  const float sixth = amax >= 0x1p-120f ? div_exact<1>(amax, RcpDivisor{6.0f, 0x1.555556p-3f, true})
-                                        : __fdiv_rn(amax, 6.0f);
+  const float sixth = sixth_of(amax);
 
   uint32_t sbyte;
   float eff;            // effective block scale (what q divides by)
   if (FMT == kMX) {
-    int k;
-    if (sixth != sixth) {
-      sbyte = 0xFFu;
-      k = 0;
-    } else {
-      if (sixth == 0.0f) k = -127;
-      else if (sixth > 3.4028234e38f) k = 127;
-      else k = ceil_log2_pos(sixth);
-      k = k < -127 ? -127 : (k > 127 ? 127 : k);
-      sbyte = (uint32_t)(k + 127);
-    }
-    // 2^-k as fp32 (2^-127 is subnormal, 2^127 normal): exact
-    const float inv = (k == 127) ? __uint_as_float(0x00400000u) : __uint_as_float((uint32_t)(127 - k) << 23);
-    eff = (sbyte == 0xFFu) ? __uint_as_float(0x7FC00000u) : inv;   // used as a multiplier below
+    sbyte = mx_scale_byte(sixth, &eff);       // eff is used as a multiplier below
   } else {
     float ws2;
     RcpDivisor wd;
@@ -304,8 +310,7 @@ __device__ __forceinline__ void rtn_block16_nv(const uint4 lo, const uint4 hi, i
   for (int k = 0; k < 8; ++k) m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(u16x2, h[k] & 0x7FFF7FFFu));
   const uint32_t am = max((uint32_t)m2[0], (uint32_t)m2[1]);
   const float amax = __uint_as_float(am << 16);
-  const float sixth = amax >= 0x1p-120f ? div_exact<1>(amax, RcpDivisor{6.0f, 0x1.555556p-3f, true})
-                                        : __fdiv_rn(amax, 6.0f);
+  const float sixth = sixth_of(amax);
   const uint32_t sbyte = e4m3_encode_rne_sat(div_exact<NVFAST>(sixth, wd));
   const uint32_t ti = 2u * (sbyte & 127u);          // sbyte <= 0x7F: sixth / ws2 is never negative
   const float eff = tab[ti];
@@ -438,22 +443,9 @@ __device__ __forceinline__ uint32_t rtn_block32_mx(const uint32_t (&h)[16], uint
   for (int k = 0; k < 16; ++k) m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(u16x2, h[k] & 0x7FFF7FFFu));
   const uint32_t am = max((uint32_t)m2[0], (uint32_t)m2[1]);
   const float amax = __uint_as_float(am << 16);
-  const float sixth = amax >= 0x1p-120f ? div_exact<1>(amax, RcpDivisor{6.0f, 0x1.555556p-3f, true})
-                                        : __fdiv_rn(amax, 6.0f);
-  uint32_t sbyte;
-  float inv;                                        // 2^-k; NaN for a NaN block
-  if (sixth != sixth) {
-    sbyte = 0xFFu;
-    inv = __uint_as_float(0x7FC00000u);
-  } else {
-    int k;
-    if (sixth == 0.0f) k = -127;
-    else if (sixth > 3.4028234e38f) k = 127;
-    else k = ceil_log2_pos(sixth);
-    k = k < -127 ? -127 : (k > 127 ? 127 : k);
-    sbyte = (uint32_t)(k + 127);
-    inv = (k == 127) ? __uint_as_float(0x00400000u) : __uint_as_float((uint32_t)(127 - k) << 23);
-  }
+  const float sixth = sixth_of(amax);
+  float inv;
+  const uint32_t sbyte = mx_scale_byte(sixth, &inv);
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
     float q[8];
