@@ -397,7 +397,7 @@ SQ_EXPORT int sq_qast_factor_grads_batched(int64_t E, int64_t O, int64_t G, int 
 
 namespace {
 constexpr int kLoraRankMax = 64;
-constexpr int64_t kRequantRowsMax = int64_t(65535) * 16;     // grid.y of the fused re-quantiser
+constexpr int64_t kRequantRowsMax = int64_t(65535) * 16;     // well inside grid.y: 64 rows per workgroup
 constexpr int64_t kLoraTokensMax = int64_t(65535) * 128;     // grid.y of the token-chunk kernel
 
 int check_lora_dims(int64_t T, int64_t O, int64_t I, int r) {

@@ -124,12 +124,6 @@ __device__ __forceinline__ void dma16(DmaRsrc r, SQ_LDS void* dst, uint32_t voff
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(r.v)
                : "memory", "m0");
 }
-// 4 bytes per lane; lane l writes dst + 4 l.
-__device__ __forceinline__ void dma4(DmaRsrc r, SQ_LDS void* dst, uint32_t voff) {
-  const int lds = __builtin_amdgcn_readfirstlane((int)(uint32_t)reinterpret_cast<uintptr_t>(dst));
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(r.v)
-               : "memory", "m0");
-}
 
 // Wait until at most n vector-memory loads of this wave are outstanding and
 // all of its LDS operations are done (raw s_barrier has no memory semantics).
