@@ -46,7 +46,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // so that a lane ends with four consecutive bytes of one row, one word each
 // way.  Else its operands change places: a lane ends with one byte of each of
 // four rows, and 16 lanes with 16 consecutive bytes of a row (14336 x 129 at
-// rank 58, NVFP4: 26.8 -> 17.3 us, 128 experts of 1536 x 65 at rank 2 54.2 -> 36.2,
+// rank 58, NVFP4: 27.0 -> 18.0 us, 128 experts of 1536 x 65 at rank 2 54.2 -> 36.2,
 // against vector multiply-adds fed from LDS).
 
 // The sums s[0..3] of a lane to scales: blocks g .. g + 3 of row o (vec), or
@@ -136,49 +136,66 @@ struct ATile {
 // block and four ranks per MFMA (v_mfma_f32_16x16x4 adds its four terms in
 // increasing k, each with its own rounding: every byte the tests compare
 // depends on it).  GB of a workgroup's four waves lie along g, the rest along
-// o.  A workgroup's rows of B and columns of A come through LDS, since a load
-// per rank and lane cost more than the products from rank 32 on (4096 x 256 at
-// rank 64 11.8 us so, 8.8 through LDS).  4096 x 256 scales at rank 58, NVFP4: 10.1
-// us on vector multiply-adds fed from LDS, 7.3 here; 4096 x 293 8.3 -> 7.1 at rank
-// 26, 7384 x 77 5.7 -> 5.2 at rank 11.
-template <int FMT, int RMAX, int GB>
+// o.  STAGED: a workgroup's rows of B and columns of A come through LDS in wide
+// loads, since at high ranks a load per rank and lane costs more than the
+// products (4096 x 256 at rank 64 11.5 us so, 8.8 through LDS; scales_staged has
+// the line).  4096 x 256 scales at rank 58, NVFP4: 10.1 us on vector multiply-adds
+// fed from LDS, 7.3 here; 7384 x 77 5.7 -> 4.9 at rank 11.
+template <int FMT, int RMAX, int GB, bool STAGED>
 __global__ __launch_bounds__(256, 4) void qast_scales_kernel(const uint8_t* __restrict__ base,
                                                           const uint16_t* __restrict__ B,
                                                           const uint16_t* __restrict__ A, int O, int G, int r,
                                                           float c, Ws2Table ws2, uint8_t* out, uint8_t* mask,
                                                           int vec, int w) {
-  constexpr int COLS = 16 * GB, ROWS = 64 / GB;
-  __shared__ uint16_t at_lds[RMAX][COLS];
-  __shared__ __attribute__((aligned(16))) uint16_t b_lds[ROWS * RMAX];
+  constexpr int COLS = 16 * GB, ROWS = 64 / GB, N = RMAX / 4;
+  __shared__ uint16_t at_lds[STAGED ? RMAX : 1][COLS];
+  __shared__ __attribute__((aligned(16))) uint16_t b_lds[STAGED ? ROWS * RMAX : 8];
   const int e = blockIdx.y;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4;
   const int gtiles = (G + COLS - 1) / COLS;
   const int gw = (int)blockIdx.x % gtiles * COLS, ow = (int)blockIdx.x / gtiles * ROWS;   // of the workgroup
   const int g0 = gw + wave % GB * 16, ro = wave / GB * 16, o0 = ow + ro;
   const size_t rows0 = (size_t)e * O;
-  ATile<RMAX, COLS> at;
-  at.load(A + (size_t)e * r * G, gw, G, r);
-  stage_run(b_lds, B + (rows0 + ow) * r, min(ROWS, O - ow) * r, w);
+  const bool g_ok = g0 + n < G, o_ok = o0 + n < O;
   const int g = vec ? g0 + 4 * q : g0 + n, o = vec ? o0 + n : o0 + 4 * q;
   uint32_t in[4];
-  base4(in, base, rows0, o, g, O, G, vec);
-  at.store(at_lds, gw, G, r);
-  const Ws2Div wd = make_ws2_div(ws2.v[e]);
-  __syncthreads();
-  const bool o_ok = o0 + n < O;
-  const uint16_t* bl = b_lds + (o_ok ? (ro + n) * r : 0);
-  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-  auto multiply = [&](auto VEC) {
+  uint16_t ar[N], br[N];
+  ATile<RMAX, COLS> at;
+  if constexpr (STAGED) {
+    at.load(A + (size_t)e * r * G, gw, G, r);
+    base4(in, base, rows0, o, g, O, G, vec);            // before the wait for B, whose loads go straight on to LDS
+    stage_run(b_lds, B + (rows0 + ow) * r, min(ROWS, O - ow) * r, w);
+  } else {
+    const uint16_t* ap = A + (size_t)e * r * G + (g_ok ? g0 + n : 0);
+    const uint16_t* bp = B + (rows0 + (o_ok ? o0 + n : 0)) * r;
 #pragma unroll
-    for (int st = 0; st < RMAX / 4; ++st) {
-      const int k = 4 * st + q;                          // ranks past r add exact zeros
-      const float av = bf16_bits_to_f32(at_lds[k][wave % GB * 16 + n]);
-      const float bv = o_ok && k < r ? bf16_bits_to_f32(bl[k < r ? k : 0]) : 0.0f;
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(VEC ? av : bv, VEC ? bv : av, acc, 0, 0, 0);
+    for (int st = 0; st < N; ++st) {
+      const int k = 4 * st + q, kc = k < r ? k : 0;
+      ar[st] = ap[(size_t)kc * G];
+      br[st] = bp[kc];
     }
-  };
-  if (vec) multiply(std::true_type{});
-  else multiply(std::false_type{});
+  }
+  if constexpr (!STAGED) base4(in, base, rows0, o, g, O, G, vec);
+  if constexpr (STAGED) at.store(at_lds, gw, G, r);
+  const Ws2Div wd = make_ws2_div(ws2.v[e]);
+  if constexpr (STAGED) {
+    __syncthreads();
+    const uint16_t* bl = b_lds + (o_ok ? (ro + n) * r : 0);
+#pragma unroll
+    for (int st = 0; st < N; ++st) {
+      const int k = 4 * st + q;
+      ar[st] = at_lds[k][wave % GB * 16 + n];
+      br[st] = bl[k < r ? k : 0];
+    }
+  }
+  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int st = 0; st < N; ++st) {
+    const bool in_r = 4 * st + q < r;                    // ranks past r add exact zeros
+    const float av = g_ok && in_r ? bf16_bits_to_f32(ar[st]) : 0.0f;
+    const float bv = o_ok && in_r ? bf16_bits_to_f32(br[st]) : 0.0f;
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(vec ? av : bv, vec ? bv : av, acc, 0, 0, 0);
+  }
   const float sum[4] = {acc[0], acc[1], acc[2], acc[3]};
   scale4<FMT>(sum, in, c, wd, out, mask, rows0, o, g, O, G, vec);
 }
@@ -188,7 +205,7 @@ __global__ __launch_bounds__(256, 4) void qast_scales_kernel(const uint8_t* __re
 // (v_mfma_f32_16x16x1: a register of A and one of B per rank serve all four),
 // GB of them along g; the workgroup's waves lie below one another and share
 // the A columns, of which each loads a quarter of the ranks into LDS; a row
-// of B comes W ranks per load or, at odd ranks and where VEC is off, through
+// of B comes W ranks per load or, at odd ranks, through
 // LDS, since the rows of a workgroup are one run of memory (16 experts of 1536 x
 // 64 at rank 31, NVFP4: 8.1 us, 9.0 on vector multiply-adds).  128 experts of
 // 768 x 128 scales at rank 58 (NVFP4): 85 us on vector multiply-adds fed from
@@ -212,7 +229,6 @@ __global__ __launch_bounds__(256, 4) void qast_scales_wide_kernel(const uint8_t*
   const size_t rows0 = (size_t)e * O;
   ATile<RMAX, COLS> at;
   at.load(A + (size_t)e * r * G, g0, G, r);
-  if constexpr (W == 1) stage_run(b_lds, B + (rows0 + ow) * r, min(ROWS, O - ow) * r, w);
   const int rl = 16 * (q / GB) + n;                     // this lane's operand row
   const bool o_ok = o0 + rl < O;
   uint32_t br[W > 1 ? RMAX / 2 : 1];                    // pairs of ranks
@@ -239,6 +255,7 @@ __global__ __launch_bounds__(256, 4) void qast_scales_wide_kernel(const uint8_t*
   uint32_t in[4][4];
 #pragma unroll
   for (int b = 0; b < 4; ++b) base4(in[b], base, rows0, row(b), blk(b), O, G, VEC);
+  if constexpr (W == 1) stage_run(b_lds, B + (rows0 + ow) * r, min(ROWS, O - ow) * r, w);
   at.store(at_lds, g0, G, r);
   __syncthreads();
   const uint16_t* bl = b_lds + (W == 1 && o_ok ? (ro + rl) * r : 0);
@@ -290,6 +307,12 @@ __global__ __launch_bounds__(256, 4) void qast_scales_wide_kernel(const uint8_t*
 // moved every operand through them (128 experts of 2048 x 24 at rank 32: the
 // gradients 45 -> 36 us).
 constexpr int kDaRows = 64;         // rows per dA chunk
+// Workgroups from which on dA of narrow dS rows (no vec) takes columns 16 u + n of
+// the block tile instead of U n + u, one run of dS per load (128 experts of 1536 x
+// 65 at rank 5 79 -> 67 us, 16 of 7384 x 77 52 -> 47; below, a lane's own
+// neighbours serve better: 1536 x 65 8.1 against 9.1, 16 experts of 2048 x 130 at
+// rank 32 37 against 40).
+constexpr int64_t kDaRunsGrid = 4096;
 template <int RT>
 __host__ __device__ constexpr int da_u() { return RT == 4 ? 2 : 4; }
 
@@ -392,7 +415,7 @@ __device__ __forceinline__ void db_tile(int bx, int e, float* lds, const float* 
   }
 }
 
-template <int RT>
+template <int RT, bool RUNS>
 __device__ __forceinline__ void da_tile(int bx, int e, float* lds, const float* __restrict__ dS,
                                         const uint8_t* __restrict__ mask, const uint16_t* __restrict__ B, int O,
                                         int G, int r, float* __restrict__ part, int vec, int bvec) {
@@ -415,7 +438,7 @@ __device__ __forceinline__ void da_tile(int bx, int e, float* lds, const float* 
 #pragma unroll
   for (int st = 0; st < 4; ++st) {
     const int o = o0 + 4 * st + q, k0 = RT * n;
-    if (vec) {
+    if constexpr (!RUNS) {
       load_v<U>(v[st], dS, mask, O, G, o, g0 + U * n, vec);
     } else {
 #pragma unroll
@@ -443,11 +466,11 @@ __device__ __forceinline__ void da_tile(int bx, int e, float* lds, const float* 
 #pragma unroll
       for (int u = 0; u < U; ++u)
         acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[st][t], v[st][u], acc[t][u], 0, 0, 0);
-  // register x of tile (t, u): rank RT (4 q + x) + t, block U n + u.  Waves 2
+  // register x of tile (t, u): rank RT (4 q + x) + t, column U n + u of LDS.  Waves 2
   // and 3 park their sums, waves 0 and 1 add theirs (half the LDS of four
   // planes, so twice the workgroups per CU), then the two planes are added.
   auto at = [&](int w, int t, int x, int u) -> float& {
-    return lds[(w * 16 * RT + RT * (4 * q + x) + t) * S + (vec ? U * n + u : 16 * u + n)];
+    return lds[(w * 16 * RT + RT * (4 * q + x) + t) * S + U * n + u];
   };
   if (wave >= 2) {
 #pragma unroll
@@ -469,11 +492,12 @@ __device__ __forceinline__ void da_tile(int bx, int e, float* lds, const float* 
   __syncthreads();
   for (int i = threadIdx.x; i < r * COLS; i += 256) {
     const int k = i / COLS, gi = i % COLS;
-    if (g0 + gi < G) part[((size_t)chunk * r + k) * G + g0 + gi] = lds[k * S + gi] + lds[(16 * RT + k) * S + gi];
+    const int at_ = k * S + (RUNS ? U * (gi % 16) + gi / 16 : gi);
+    if (g0 + gi < G) part[((size_t)chunk * r + k) * G + g0 + gi] = lds[at_] + lds[16 * RT * S + at_];
   }
 }
 
-template <int RT>
+template <int RT, bool RUNS>
 __global__ __launch_bounds__(256, 4) void qast_grads_kernel(const float* __restrict__ dS,
                                                          const uint8_t* __restrict__ mask,
                                                          const uint16_t* __restrict__ A,
@@ -486,7 +510,7 @@ __global__ __launch_bounds__(256, 4) void qast_grads_kernel(const float* __restr
   if (bx < ndb)
     db_tile<RT>(bx, e, lds, dS, mask, A, O, G, r, c, dB, vec);
   else
-    da_tile<RT>(bx - ndb, e, lds, dS, mask, B, O, G, r, part, vec, bvec);
+    da_tile<RT, RUNS>(bx - ndb, e, lds, dS, mask, B, O, G, r, part, vec, bvec);
 }
 
 // dA[i] = c sum over the chunk partials in order.  64 consecutive outputs per
@@ -523,26 +547,38 @@ __global__ __launch_bounds__(256) void qast_da_reduce_kernel(const float* __rest
 // 12.2 and 14,336 (4096 x 896) 13.2 against 21.0.
 constexpr int64_t kScWideBlocks = 6144;
 
+// Whether the narrow kernel's factors come through LDS: in 16-byte loads from rank
+// 32 on (4096 x 64 at rank 48 5.2 us a rank per load, 4.9 so, at rank 24 3.8 and
+// 4.0), and where workgroups share the CUs from rank 16 on (4096 x 256 at rank 16
+// 5.7 and 5.2, at rank 8 4.2 and 4.8) or, at odd ranks, in the 64-rank kernel
+// (rank 63 8.5 and 7.6, rank 31 6.3 and 6.2, rank 11 4.6 and 5.2).
+static bool scales_staged(int r, int w, int64_t grid) {
+  if (grid <= 512) return w == 8 && r >= 32;
+  return w > 1 ? r >= 16 : r > 32;
+}
+
 template <int F, int R, int GB>
 static void scales_go(bool wide, int w, int64_t gtiles, int m, hipStream_t s, const uint8_t* bp, const uint16_t* Bp,
                       const uint16_t* Ap, int O, int G, int r, float c, const Ws2Table& t, uint8_t* op, uint8_t* mp,
                       int vec) {
   const int rows = (wide ? 4 : 1) * 16 * (4 / GB);                   // of a workgroup
   const dim3 grid((unsigned)(((O + rows - 1) / rows) * gtiles), (unsigned)m);
-  if (!wide)
-    hipLaunchKernelGGL((qast_scales_kernel<F, R, GB>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op, mp, vec, w);
-  else if (!vec)
-    hipLaunchKernelGGL((qast_scales_wide_kernel<F, R, GB, 1, false>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op,
-                       mp, w);
-  else if (w == 8)
-    hipLaunchKernelGGL((qast_scales_wide_kernel<F, R, GB, 8, true>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op,
-                       mp, w);
-  else if (w == 2)
-    hipLaunchKernelGGL((qast_scales_wide_kernel<F, R, GB, 2, true>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op,
-                       mp, w);
-  else
-    hipLaunchKernelGGL((qast_scales_wide_kernel<F, R, GB, 1, true>), grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op,
-                       mp, w);
+  const auto go = [&](auto k, auto... last) {
+    hipLaunchKernelGGL(k, grid, dim3(256), 0, s, bp, Bp, Ap, O, G, r, c, t, op, mp, last...);
+  };
+  if (wide && vec) {
+    if (w == 8) go(qast_scales_wide_kernel<F, R, GB, 8, true>, w);
+    else if (w == 2) go(qast_scales_wide_kernel<F, R, GB, 2, true>, w);
+    else go(qast_scales_wide_kernel<F, R, GB, 1, true>, w);
+  } else if (wide) {
+    if (w == 8) go(qast_scales_wide_kernel<F, R, GB, 8, false>, w);
+    else if (w == 2) go(qast_scales_wide_kernel<F, R, GB, 2, false>, w);
+    else go(qast_scales_wide_kernel<F, R, GB, 1, false>, w);
+  } else if (R > 8 && scales_staged(r, w, (int64_t)grid.x * m)) {
+    go(qast_scales_kernel<F, R, GB, (R > 8)>, vec, w);
+  } else {
+    go(qast_scales_kernel<F, R, GB, false>, vec, w);
+  }
 }
 template <int F, int R>
 static void scales_gb(bool wide, int gb, int w, int m, hipStream_t s, const uint8_t* bp, const uint16_t* Bp,
@@ -605,8 +641,10 @@ static void qast_grads_r(int E, int O, int G, int r, const float* dS, const uint
   const int vec = G % 4 == 0 && al(dS, 16) && al(A, 8) && (mask == nullptr || al(mask, 4)) ? 1 : 0;
   const int ndb = G > 64 ? (O + 15) / 16 : (O + 63) / 64, nda = ((G + 16 * da_u<RT>() - 1) / (16 * da_u<RT>())) * chunks;
   const int bvec = r % 2 == 0 && al(B, 4) ? 1 : 0;
-  hipLaunchKernelGGL((qast_grads_kernel<RT>), dim3((unsigned)(ndb + nda), (unsigned)E), dim3(256), 0, s, dS, mask, A, B,
-                     O, G, r, c, dB, part, ndb, vec, bvec);
+  const bool runs = !vec && (int64_t)(ndb + nda) * E >= kDaRunsGrid;
+  hipLaunchKernelGGL((runs ? qast_grads_kernel<RT, true> : qast_grads_kernel<RT, false>),
+                     dim3((unsigned)(ndb + nda), (unsigned)E), dim3(256), 0, s, dS, mask, A, B, O, G, r, c, dB, part,
+                     ndb, vec, bvec);
   const int64_t n = (int64_t)E * r * G;
   hipLaunchKernelGGL(qast_da_reduce_kernel, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, s, part, chunks, r, G, E, c,
                      dA);
