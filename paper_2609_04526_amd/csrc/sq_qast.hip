@@ -205,13 +205,13 @@ __global__ __launch_bounds__(256, 4) void qast_scales_kernel(const uint8_t* __re
 // (v_mfma_f32_16x16x1: a register of A and one of B per rank serve all four),
 // GB of them along g; the workgroup's waves lie below one another and share
 // the A columns, of which each loads a quarter of the ranks into LDS; a row
-// of B comes W ranks per load or, at odd ranks, through
-// LDS, since the rows of a workgroup are one run of memory (16 experts of 1536 x
-// 64 at rank 31, NVFP4: 8.1 us, 9.0 on vector multiply-adds).  128 experts of
-// 768 x 128 scales at rank 58 (NVFP4): 85 us on vector multiply-adds fed from
-// LDS, 44 here, at rank 64 86 -> 34; at rank 5, where the bytes bound it, 20.9 ->
-// 22.1.  VEC is a parameter: with both orders of the operands in one kernel the
-// compiler spilled (77 us instead of 29 for 128 experts of 2048 x 24 at rank 58).
+// of B comes W ranks per load or, at odd ranks, through LDS, since the rows of a
+// workgroup are one run of memory (128 experts of 768 x 128 at rank 47 76 us a rank
+// per load, 41 so).  128 experts of 768 x 128 scales at rank 58 (NVFP4): 85 us on
+// vector multiply-adds fed from LDS, 44 here, at rank 64 86 -> 35; at rank 5, where
+// the bytes bound it, 21.8 -> 22.1.  VEC is a parameter: with both orders of the
+// operands in one kernel the compiler spilled (128 experts of 2048 x 24 at rank 58
+// 77 us instead of 29).
 template <int FMT, int RMAX, int GB, int W, bool VEC>
 __global__ __launch_bounds__(256, 4) void qast_scales_wide_kernel(const uint8_t* __restrict__ base,
                                                                const uint16_t* __restrict__ B,
@@ -541,11 +541,19 @@ __global__ __launch_bounds__(256) void qast_da_reduce_kernel(const float* __rest
 }
 
 // ------------------------------------------------------------------ launch
-// 16 x 16 blocks of a launch from which on the wide kernel is the faster one:
-// 2048 blocks (4096 x 128, rank 32) 7.2 us there against 5.8, 4096 (4096 x
-// 256, rank 58) 10.6 against 9.6, but 7168 (14336 x 128, rank 32) 9.8 against
-// 12.2 and 14,336 (4096 x 896) 13.2 against 21.0.
-constexpr int64_t kScWideBlocks = 6144;
+// Whether a launch of so many 16 x 16 blocks takes the wide kernel, by the width of
+// the loads of B's rows.  Eight ranks: 4096 blocks (4096 x 256, rank 32) 6.0 us
+// either way, 6144 (16 experts of 1536 x 64, rank 32) 7.2 there and 7.5 on the
+// narrow kernel, 7168 7.2 and 7.8.  Two: 9216 (48 experts of 768 x 64, rank 58)
+// 15.0 and 13.2, 12,288 (64 experts) 15.3 and 16.3.  One: 12,288 at rank 31 10.8 and
+// 13.4, but at rank 5 8.4 and 7.3 (24,576 13.0 and 12.7, at 128 experts of 768 x 128
+// 22.1 and 23.0); without words of bytes never (128 experts of 1536 x 65 at rank
+// 31 61.5 and 47.5).
+static bool scales_wide(int64_t blocks, int r, int w, int vec) {
+  if (w == 8) return blocks >= 6144;
+  if (w == 2) return blocks >= 12288;
+  return vec && blocks >= (r > 8 ? 12288 : 24576);
+}
 
 // Whether the narrow kernel's factors come through LDS: in 16-byte loads from rank
 // 32 on (4096 x 64 at rank 48 5.2 us a rank per load, 4.9 so, at rank 24 3.8 and
@@ -572,8 +580,7 @@ static void scales_go(bool wide, int w, int64_t gtiles, int m, hipStream_t s, co
     else go(qast_scales_wide_kernel<F, R, GB, 1, true>, w);
   } else if (wide) {
     if (w == 8) go(qast_scales_wide_kernel<F, R, GB, 8, false>, w);
-    else if (w == 2) go(qast_scales_wide_kernel<F, R, GB, 2, false>, w);
-    else go(qast_scales_wide_kernel<F, R, GB, 1, false>, w);
+    else go(qast_scales_wide_kernel<F, R, GB, 2, false>, w);
   } else if (R > 8 && scales_staged(r, w, (int64_t)grid.x * m)) {
     go(qast_scales_kernel<F, R, GB, (R > 8)>, vec, w);
   } else {
@@ -609,8 +616,8 @@ int qast_scales_launch(int fmt, int E, int O, int G, int r, const uint8_t* base,
     const uint16_t* Ap = a + (size_t)e0 * r * G;
     uint8_t* op = out + rows0 * G;
     uint8_t* mp = mask ? mask + rows0 * G : nullptr;
-    const bool wide = (int64_t)cols * ((O + 15) / 16) * m >= kScWideBlocks;
     const int vec = G % 4 == 0 && al(bp, 4) && al(op, 4) && (mp == nullptr || al(mp, 4)) ? 1 : 0;
+    const bool wide = scales_wide((int64_t)cols * ((O + 15) / 16) * m, r, w, vec);
 #define SQ_QAST_SCALES(F, R) scales_gb<F, R>(wide, gb, w, m, s, bp, Bp, Ap, O, G, r, c, t, op, mp, vec)
     if (fmt == kMX) {
       if (r <= 8) SQ_QAST_SCALES(kMX, 8);

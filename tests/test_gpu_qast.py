@@ -220,21 +220,26 @@ def test_batched_experts_match_per_expert(sq, fmt, E, O, G, r):
         assert normwise(dB[e].cpu().numpy(), wB) <= TOL and normwise(dA[e].cpu().numpy(), wA) <= TOL
 
 
-def wide_tiles_taken(E, O, G):
-    """Whether a batched call of this shape runs the scale step's wide tiles: four
-    16 x 16 blocks per wave, from 6144 such blocks on."""
-    return E * -(-O // 16) * -(-G // 16) >= 6144
+def wide_tiles_taken(E, O, G, r):
+    """Whether a batched call of this shape on aligned planes runs the scale step's wide
+    tiles (four 16 x 16 blocks per wave): by the blocks and the width of the loads of B."""
+    blocks = E * -(-O // 16) * -(-G // 16)
+    if r % 2 == 0:
+        return blocks >= (6144 if r % 8 == 0 else 12288)
+    return G % 4 == 0 and blocks >= (12288 if r > 8 else 24576)
 
 
-@pytest.mark.parametrize("fmt,E,O,G,r", [("mx", 130, 520, 40, 32), ("nv", 130, 520, 37, 33)])
+@pytest.mark.parametrize("fmt,E,O,G,r", [("mx", 130, 520, 40, 32), ("nv", 130, 520, 37, 33),
+                                         ("nv", 130, 520, 37, 34), ("nv", 130, 520, 40, 13)])
 def test_batched_wide_tiles(sq, fmt, E, O, G, r):
     """Stacked experts at MoE-like sizes, where the batched calls take the wide
     tiles (G % 4 == 0: word-wide byte planes and 16-byte dS loads; G = 37:
-    byte-wide, ragged last block tile; rank 33: the 64-rank kernels).  Every
+    byte-wide, ragged last block tile, at rank 33 on the narrow tiles; ranks 33
+    and 34: the 64-rank kernels).  Every
     expert's bytes, mask and gradients equal the single-plane calls' (narrow
     tiles) bit for bit, and sampled experts equal the oracle."""
     print(f"[qast wide] fmt={fmt} E={E} O={O} G={G} r={r}", flush=True)
-    assert wide_tiles_taken(E, O, G) and not wide_tiles_taken(1, O, G)
+    assert wide_tiles_taken(E, O, G, r) == (r != 33) and not wide_tiles_taken(1, O, G, r)
     bases, ws2s, Bs, As = [], [], [], []
     for e in range(E):
         base, ws2 = plane(fmt, O, G, 8100 + e)

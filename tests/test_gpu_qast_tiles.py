@@ -35,9 +35,12 @@ def shifted(t, nbytes):
 
 CASES = [("mx", 8, 1, 1), ("nv", 15, 15, 2), ("mx", 16, 16, 4), ("nv", 17, 17, 5), ("mx", 63, 32, 16), ("nv", 65, 33, 17),
          ("mx", 64, 48, 33), ("nv", 128, 64, 64), ("mx", 129, 65, 58), ("nv", 40, 80, 34),
-         # enough 16 x 16 blocks for the wide kernel (6144), ranks 8, 2 and 1 to a load
-         ("nv", 8200, 196, 24), ("mx", 16400, 97, 30), ("nv", 49200, 20, 7),
-         ("mx", 8200, 196, 64), ("nv", 8200, 197, 63), ("mx", 8200, 196, 61), ("nv", 100, 1000, 40), ("mx", 120, 13201, 3),
+         # enough 16 x 16 blocks for the wide kernel at ranks 8 (6144), 2 (12,288) and 1 to a load (24,576 up to rank 8)
+         ("nv", 8200, 196, 24), ("mx", 8200, 197, 64), ("mx", 28200, 97, 30), ("nv", 12300, 252, 58), ("mx", 12300, 256, 61),
+         ("nv", 24600, 256, 7),
+         # and launches that stay on the narrow one
+         ("mx", 16400, 97, 30), ("nv", 49200, 20, 7), ("nv", 8200, 197, 63), ("mx", 8200, 196, 61), ("nv", 28200, 97, 5),
+         ("mx", 8200, 196, 64), ("nv", 100, 1000, 40), ("mx", 120, 13201, 3),
          # narrow, factors through LDS by 8, 2 and 1 (over 512 workgroups), and a rank per load beside them
          ("mx", 8192, 130, 48), ("nv", 8192, 130, 20), ("mx", 8192, 130, 41), ("nv", 8192, 130, 19),
          # dA columns in runs (narrow dS rows, 4096 workgroups and more), both column counts
