@@ -1586,9 +1586,7 @@ int gemm_fwd(int fmt, int T, int O, int I, const void* X, const uint8_t* codes,
   g.M = T; g.N = O; g.K = I;
   g.ws2 = (fmt == kNV) ? ws2 : 1.0f;
   g.out_bf16 = y_bf16;
-  // tiles dequantise in registers when the code and scale planes are 16-byte
-  // aligned and every row's scales split into 16-byte runs; strips follow the
-  // order of the tiles that the call would have taken
+  // strips follow the order of the tiles that the call would have taken
   ExpertProblem one{};
   one.codes = codes;
   one.scales = scales;
