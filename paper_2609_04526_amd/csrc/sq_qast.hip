@@ -295,7 +295,8 @@ __global__ __launch_bounds__(256, 4) void qast_scales_wide_kernel(const uint8_t*
 // workgroup takes 16 U blocks and all ranks, its waves 16 rows each, four per
 // MFMA in increasing order; the waves' sums again meet in LDS in a fixed
 // order.  Column n of tile u is block U n + u, so that a lane's blocks are one
-// load of dS, and row n of tile t is rank RT n + t.  U = 4, but 2 for ranks over
+// load of dS (RUNS: block 16 u + n, see kDaRunsGrid), and row n of tile t is rank
+// RT n + t.  U = 4, but 2 for ranks over
 // 32: with 16 accumulator tiles a wave, too few waves fit a SIMD (128 experts
 // of 768 x 128 at rank 54: 113 us, 69 with 8).  Chunks are added in order by
 // qast_da_reduce_kernel.

@@ -230,12 +230,13 @@ def wide_tiles_taken(E, O, G, r):
 
 
 @pytest.mark.parametrize("fmt,E,O,G,r", [("mx", 130, 520, 40, 32), ("nv", 130, 520, 37, 33),
-                                         ("nv", 130, 520, 37, 34), ("nv", 130, 520, 40, 13)])
+                                         ("nv", 130, 520, 37, 34), ("nv", 130, 520, 40, 13),
+                                         ("mx", 130, 1040, 37, 34), ("nv", 130, 1040, 37, 20)])
 def test_batched_wide_tiles(sq, fmt, E, O, G, r):
     """Stacked experts at MoE-like sizes, where the batched calls take the wide
     tiles (G % 4 == 0: word-wide byte planes and 16-byte dS loads; G = 37:
     byte-wide, ragged last block tile, at rank 33 on the narrow tiles; ranks 33
-    and 34: the 64-rank kernels).  Every
+    and 34: the 64-rank kernels; 1040 rows: dA columns in runs).  Every
     expert's bytes, mask and gradients equal the single-plane calls' (narrow
     tiles) bit for bit, and sampled experts equal the oracle."""
     print(f"[qast wide] fmt={fmt} E={E} O={O} G={G} r={r}", flush=True)
